@@ -163,8 +163,8 @@ int dwa_apply_Dbb_dag(dwa_ctx *ctx, int prec, void *out_b, const void *in_b);
 
 /* dwa_apply_Dbb for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same operator and
- * kernels, bitwise the same result, but its two intermediate half fields (B G in, black,
- * and the first hop's output, red) live in a static 64 MiB device array of the library
+ * kernels, bitwise the same result, but its two intermediate half fields (one black, and the
+ * first hop's output, red) live in a static 64 MiB device array of the library
  * (one per GPU, set up by dwa_create and held until the process ends) instead of the
  * context's workspace.  The call allocates nothing.  Limit: the two fields, each rounded up
  * to 256 bytes, must fit in 64 MiB (FP64 at 8^3 x 16, L_s = 12 takes 18.9 MB; BF16 at
@@ -178,7 +178,9 @@ int dwa_apply_Dbb_static(dwa_ctx *ctx, int prec, void *out_b, const void *in_b);
  * of eq.(wilson) without its -1/2, taken from the parity 1 - parity_out to parity_out
  * on every slice, and M_kind is a fifth-dimension matrix of dwa_debug_smatrix (kinds
  * 0..6; 0 = identity runs the hop alone).  D_bb is built from two such launches
- * (kinds 2 and 3) and D_bb^dag from kinds 5 and 6.  Half fields of precision prec;
+ * (kinds 2 and 3) and D_bb^dag from kinds 5 and 6, except where a hop with one wavefront
+ * per site is the faster one (small lattices, BF16, and the Ls between 2 and 16 other than
+ * 4, 8, 12, 16), which applies the same matrices in another order.  Half fields of precision prec;
  * out and in must not overlap.  Exposed for measurement and tests. */
 int dwa_apply_hop(dwa_ctx *ctx, int prec, int parity_out, int kind, void *out, const void *in);
 
@@ -189,7 +191,8 @@ int dwa_apply_hop(dwa_ctx *ctx, int prec, int parity_out, int kind, void *out, c
  * order, 2 = z-planes per XCD.  Only the assignment of sites to blocks changes: every
  * site's arithmetic is the same, so D_bb and every hop output are bitwise identical
  * across configurations (CG reductions group their partial sums by block, so solver
- * scalars can differ in the last bits).  The defaults are ns = 16 for FP64, 32 for
+ * scalars can differ in the last bits).  The hop with one wavefront per site has no tile: it
+ * takes the order and nf alone.  The defaults are ns = 16 for FP64, 32 for
  * FP32 / BF16, order 0. */
 typedef struct {
   int prec;  /* storage precision */
@@ -197,7 +200,7 @@ typedef struct {
   int order; /* block traversal */
   int nf;    /* fields per block when a batch is applied */
   int dense; /* 1: dense L_s x L_s fifth-dimension matrices (generic 8-site kernel),
-                0: the O(L_s) sweep programs */
+                0: the O(L_s) sweep programs, or the hop with one wavefront per site */
   int nrhs;  /* fields the configuration was timed on (1, or a batch) */
   double us; /* average time of one hop pair of D_bb (N hop, then G^-1 I^-1 hop with the
                 x term) on nrhs fields, microseconds; negative if the configuration

@@ -3,8 +3,8 @@
     python -m paper_1501_04950_amd.build
 
 Each source is compiled to an object in parallel (one translation unit per field
-precision carries the site-local kernels, and one per precision and tile size the fused
-hop), then linked into one shared library.  Device
+precision carries the site-local kernels, one the wave-per-site hop, and one per precision and tile
+size the fused hop), then linked into one shared library.  Device
 code targets gfx950 only, with packed FP32 instructions turned off.
 """
 
@@ -16,6 +16,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SOURCES = ([f"csrc/kernels_hop_{p}_{ns}.hip" for p in ("f64", "f32", "bf16") for ns in (8, 16, 32)]
+           + [f"csrc/kernels_wave_{p}.hip" for p in ("f64", "f32", "bf16")]
            + ["csrc/kernels_f64.hip", "csrc/kernels_f32.hip", "csrc/kernels_bf16.hip",
               "csrc/kernels.hip", "csrc/adjoint.hip", "csrc/scratch.hip", "csrc/api.cpp",
               "csrc/smat.cpp", "csrc/zolotarev.cpp"])
@@ -24,6 +25,8 @@ OBJDIR = os.path.join(PKG, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # matrix-core results in ordinary registers (no copies before vector instructions)
+         "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-I", os.path.join(ROOT, "include")]
 
 

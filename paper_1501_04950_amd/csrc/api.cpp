@@ -99,12 +99,46 @@ int dbbdag_from_premix(dwa_ctx* ctx, int prec, void* out, const void* in, const 
   return launch_hop(ctx, prec, b, nblocks);
 }
 
-int apply_dbb(dwa_ctx* ctx, int prec, void* out, const void* in, void* tb, void* tr, int nrhs = 1) {
+// D_bb (dag = false) or D_bb^dag of site-major fields by two wave hops; tr is a red field.
+int wave_dbb(dwa_ctx* ctx, int prec, bool dag, void* out, const void* in, void* tr, double* partials, int* nparts,
+             int nrhs = 1) {
+  const WaveOp a{in, tr, nullptr, dag ? WT_DAG1 : WT_DBB1, 1, nullptr, nrhs, false, false, false};
+  DWA_TRY(launch_wave_hop(ctx, prec, a, nullptr));
+  const WaveOp b{tr, out, in, dag ? WT_DAG2 : WT_DBB2, 0, partials, nrhs, false, false, false};
+  return launch_wave_hop(ctx, prec, b, nparts);
+}
+
+// The same on SoA fields.  Up to 2 MB, which stays in the caches, are read and written in
+// place, by 4 to 16 bytes a lane; more passes through a site-major copy of the input (tb) and
+// a tiled store, so that every access is whole lines (BF16, L_s = 8, 12 fields of 4096 sites:
+// 155 us in place, 69 us so).  The tiled store sums no
+// norms, so with partials the output is read once more.
+constexpr size_t kWaveDirectBytes = size_t(2) << 20;
+int wave_dbb_soa(dwa_ctx* ctx, int prec, bool dag, void* out, const void* in, void* tb, void* tr, int nrhs = 1,
+                 double* partials = nullptr, int* nparts = nullptr) {
+  const bool small = size_t(nrhs) * field_elems(ctx) * elem_bytes(prec) <= kWaveDirectBytes;
+  if (!small) DWA_TRY(launch_to_sm(ctx, prec, tb, prec, in, 1.0, nrhs));
+  const WaveOp a{small ? in : tb, tr, nullptr, dag ? WT_DAG1 : WT_DBB1, 1, nullptr, nrhs, small, false, false};
+  DWA_TRY(launch_wave_hop(ctx, prec, a, nullptr));
+  const WaveOp b{tr, out, small ? in : tb, dag ? WT_DAG2 : WT_DBB2, 0, nullptr, nrhs, false, small, true};
+  DWA_TRY(launch_wave_hop(ctx, prec, b, nullptr));
+  return partials ? launch_norm2(ctx, prec, out, field_elems(ctx), partials, nparts, nrhs) : DWA_OK;
+}
+
+}  // namespace
+
+namespace dwa {
+int apply_dbb(dwa_ctx* ctx, int prec, void* out, const void* in, void* tb, void* tr, int nrhs) {
+  if (use_wave_soa(ctx, prec, nrhs)) return wave_dbb_soa(ctx, prec, false, out, in, tb, tr, nrhs);
   DWA_TRY(launch_smix(ctx, prec, MIX_BG, tb, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr, nrhs));
   return dbb_from_premix(ctx, prec, out, in, tb, tr, nullptr, nullptr, nrhs);
 }
+}  // namespace dwa
+
+namespace {
 
 int apply_dbbdag(dwa_ctx* ctx, int prec, void* out, const void* in, void* tb, void* tr) {
+  if (use_wave_soa(ctx, prec, 1)) return wave_dbb_soa(ctx, prec, true, out, in, tb, tr);
   DWA_TRY(launch_smix(ctx, prec, MIX_G5_IINVT_GINV, tb, in, nullptr, 0.0, ctx->Ls, nullptr,
                       nullptr));
   return dbbdag_from_premix(ctx, prec, out, in, tb, tr, nullptr, nullptr);
@@ -207,6 +241,11 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
   DevScalars* sc = ctx->d_scal;
   int nbA = 0, nbB = 0, nbZ = 0;  // partials: bank 0 |q|^2, bank 1 |r|^2, bank 2 |z|^2
   if (check_every < 1) check_every = 1;
+  // site-major fields and wave hops, with no premixed fields (u and w); an FP64 solution is
+  // held in u until the end
+  const bool sm = use_wave(ctx, prec);
+  void* const x_out = x;
+  if (sm && p64) x = u;
 
   if (warm && !p64) {
     set_error("warm-started CGLS needs FP64 storage");
@@ -217,25 +256,35 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
   const int mixA = adj ? MIX_G5_IINVT_GINV : MIX_BG;
   const int mixAd = adj ? MIX_BG : MIX_G5_IINVT_GINV;
   auto applyA = [&](void* out, const void* in, const void* pre, double* part, int* nb) {
+    if (sm) return wave_dbb(ctx, prec, adj, out, in, t, part, nb);
     return adj ? dbbdag_from_premix(ctx, prec, out, in, pre, t, part, nb)
                : dbb_from_premix(ctx, prec, out, in, pre, t, part, nb);
   };
   auto applyAd = [&](void* out, const void* in, const void* pre, double* part, int* nb) {
+    if (sm) return wave_dbb(ctx, prec, !adj, out, in, t, part, nb);
     return adj ? dbb_from_premix(ctx, prec, out, in, pre, t, part, nb)
                : dbbdag_from_premix(ctx, prec, out, in, pre, t, part, nb);
   };
+  auto premix = [&](int kind, void* out, const void* in) {
+    return sm ? DWA_OK : launch_smix(ctx, prec, kind, out, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr);
+  };
+  // r = rhs (a low-precision right-hand side is site-major already)
+  auto load_rhs = [&]() {
+    return sm && p64 ? launch_to_sm(ctx, prec, r, prec, rhs, 1.0) : launch_axpby(ctx, prec, r, 1.0, rhs, 0.0, n);
+  };
   if (warm) {
-    DWA_TRY(launch_smix(ctx, prec, mixA, u, x, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+    if (sm) DWA_TRY(launch_to_sm(ctx, prec, x, prec, x_out, 1.0));
+    DWA_TRY(premix(mixA, u, x));
     DWA_TRY(applyA(q, x, u, nullptr, nullptr));
-    DWA_TRY(launch_axpby(ctx, prec, r, 1.0, rhs, 0.0, n));
+    DWA_TRY(load_rhs());
     DWA_TRY(launch_axpby(ctx, prec, r, -1.0, q, 1.0, n));
     res->n_dbb += 1;
   } else {
     DWA_TRY(launch_zero(ctx, xacc_prec(prec), x, n));
-    DWA_TRY(launch_axpby(ctx, prec, r, 1.0, rhs, 0.0, n));
+    DWA_TRY(load_rhs());
   }
   // z = A^dag r, gamma = |z|^2, |rhs|^2
-  DWA_TRY(launch_smix(ctx, prec, mixAd, w, r, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+  DWA_TRY(premix(mixAd, w, r));
   DWA_TRY(applyAd(z, r, w, bank(ctx, 2), &nbZ));
   DWA_TRY(launch_norm2(ctx, prec, rhs, n, bank(ctx, 1), &nbB));
   DWA_TRY(launch_cg_finalize(ctx, 2, sc, bank(ctx, 2), nbZ, bank(ctx, 1), nbB));
@@ -245,7 +294,7 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
   }
   res->n_dbb += 1;
   DWA_TRY(launch_axpby(ctx, prec, p, 1.0, z, 0.0, n));
-  DWA_TRY(launch_smix(ctx, prec, mixA, u, p, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+  DWA_TRY(premix(mixA, u, p));
 
   const double tol2 = tol * tol;
   // first half of an iteration: q = A p (premixed u), |q|^2; (a = gamma / |q|^2 from those
@@ -253,6 +302,8 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
   // (gamma = |z|^2 from the current z's partials, also inside update 1)
   auto first_half = [&]() -> int {
     DWA_TRY(applyA(q, p, u, bank(ctx, 0), &nbA));
+    if (sm)
+      return launch_vec_update1(ctx, prec, x, r, p, q, sc, bank(ctx, 1), &nbB, 1, bank(ctx, 0), nbA, bank(ctx, 2), nbZ);
     return launch_cg_update1(ctx, prec, x, r, w, p, q, sc, bank(ctx, 1), &nbB, adj, 1, bank(ctx, 0), nbA,
                              bank(ctx, 2), nbZ);
   };
@@ -260,6 +311,7 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
   // u = premix of p for A
   auto second_half = [&]() -> int {
     DWA_TRY(applyAd(z, r, w, bank(ctx, 2), &nbZ));
+    if (sm) return launch_vec_update2(ctx, prec, p, z, sc, 1, bank(ctx, 2), nbZ);
     return launch_cg_update2(ctx, prec, p, u, z, sc, adj, 1, bank(ctx, 2), nbZ);
   };
   // The host checks after x and r have been updated; between checks the body (second half
@@ -296,7 +348,7 @@ int cgls(dwa_ctx* ctx, int prec, void* x, const void* rhs, bool warm, double tol
     ++k;
   }
   res->iters = k;
-  return DWA_OK;
+  return sm && p64 ? launch_from_sm(ctx, prec, x_out, x) : DWA_OK;
 }
 
 // rho += -1/2 H chi on the two wall slices of both parities (nr fields field_elems
@@ -333,6 +385,19 @@ int true_residual64(dwa_ctx* ctx, const void* x, const void* rhs, double rhs_nor
   DWA_HIP(hipStreamSynchronize(ctx->stream), "stream sync");
   *rel = rhs_norm > 0 ? std::sqrt(rr) / rhs_norm : 0.0;
   return DWA_OK;
+}
+
+// An FP64 SoA field into the inner solver's storage and layout, and the accumulated inner
+// solution back into an FP64 SoA field (x_l is cleared).
+int to_inner(dwa_ctx* ctx, int inner, void* out, const void* in, double scale, int nrhs = 1,
+             const double* scales = nullptr) {
+  if (use_wave(ctx, inner)) return launch_to_sm(ctx, inner, out, DWA_F64, in, scale, nrhs, scales);
+  return launch_convert(ctx, inner, out, DWA_F64, in, field_elems(ctx), scale, nrhs, scales);
+}
+int fold_inner(dwa_ctx* ctx, int inner, void* X, void* xl, double scale, int nrhs = 1,
+               const double* scales = nullptr) {
+  if (use_wave(ctx, inner)) return launch_fold_sm(ctx, X, xl, scale, nrhs, scales);
+  return launch_fold_acc(ctx, xacc_prec(inner), X, xl, field_elems(ctx), scale, nrhs, scales);
 }
 
 // Mixed precision: FP64 outer defect correction around an inner CGLS in storage
@@ -376,7 +441,7 @@ int mixed_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_sol
     }
     const double rnorm = rel * bnorm;
     // low-precision rhs: r / |r|
-    DWA_TRY(launch_convert(ctx, inner, L[L_OPB], DWA_F64, W[W_RES], n, 1.0 / rnorm));
+    DWA_TRY(to_inner(ctx, inner, L[L_OPB], W[W_RES], 1.0 / rnorm));
     // inner target: delta, but not tighter than needed for the final tolerance
     double inner_tol = delta;
     const double need = 0.5 * o->tol / rel;
@@ -391,7 +456,7 @@ int mixed_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_sol
       break;
     }
     // x += |r| e  (FP64 accumulate)
-    DWA_TRY(launch_fold_acc(ctx, xacc_prec(inner), x, xacc_buf(ctx, inner), n, rnorm));
+    DWA_TRY(fold_inner(ctx, inner, x, xacc_buf(ctx, inner), rnorm));
     DWA_TRY(true_residual64(ctx, x, rhs, bnorm, &rel, W[W_RES]));
     ndbb += 1;
     ++outer;
@@ -443,11 +508,17 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
   // from p) and of A^dag (w, from r) follow
   const int mixA = adj ? MIX_G5_IINVT_GINV : MIX_BG;
   const int mixAd = adj ? MIX_BG : MIX_G5_IINVT_GINV;
+  const bool sm = use_wave(ctx, inner);  // site-major fields and wave hops (as in cgls)
+  auto premix = [&](int kind, void* out, const void* in) {
+    return sm ? DWA_OK : launch_smix(ctx, inner, kind, out, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr);
+  };
   auto applyA = [&](void* out, const void* in, const void* pre, double* part, int* nb) {
+    if (sm) return wave_dbb(ctx, inner, adj, out, in, t, part, nb);
     return adj ? dbbdag_from_premix(ctx, inner, out, in, pre, t, part, nb)
                : dbb_from_premix(ctx, inner, out, in, pre, t, part, nb);
   };
   auto applyAd = [&](void* out, const void* in, const void* pre, double* part, int* nb) {
+    if (sm) return wave_dbb(ctx, inner, !adj, out, in, t, part, nb);
     return adj ? dbb_from_premix(ctx, inner, out, in, pre, t, part, nb)
                : dbbdag_from_premix(ctx, inner, out, in, pre, t, part, nb);
   };
@@ -477,14 +548,14 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
   }
   // low-precision state, scaled so the residual starts at unit norm
   double scale = rel * bnorm;  // FP64 residual norm at the last update
-  DWA_TRY(launch_convert(ctx, inner, r, DWA_F64, W[W_RES], n, 1.0 / scale));
+  DWA_TRY(to_inner(ctx, inner, r, W[W_RES], 1.0 / scale));
   DWA_TRY(launch_zero(ctx, xprec, xl, n));
-  DWA_TRY(launch_smix(ctx, inner, mixAd, w, r, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+  DWA_TRY(premix(mixAd, w, r));
   DWA_TRY(applyAd(z, r, w, bank(ctx, 2), &nbZ));
   DWA_TRY(launch_norm2(ctx, inner, r, n, bank(ctx, 1), &nbB));
   DWA_TRY(launch_cg_finalize(ctx, 2, sc, bank(ctx, 2), nbZ, bank(ctx, 1), nbB));
   DWA_TRY(launch_axpby(ctx, inner, p, 1.0, z, 0.0, n));
-  DWA_TRY(launch_smix(ctx, inner, mixA, u, p, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+  DWA_TRY(premix(mixA, u, p));
   ndbb += 1;
 
   int k = 0, status = DWA_ENOCONV, stall = 0;
@@ -495,6 +566,9 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
   // x_l += a p ; r_l -= a q ; |r_l|^2 ; w = g5 I^-T G^-1 r_l
   auto first_half = [&]() -> int {
     DWA_TRY(applyA(q, p, u, bank(ctx, 0), &nbA));
+    if (sm)
+      return launch_vec_update1(ctx, inner, xl, r, p, q, sc, bank(ctx, 1), &nbB, 1, bank(ctx, 0), nbA, bank(ctx, 2),
+                                nbZ);
     return launch_cg_update1(ctx, inner, xl, r, w, p, q, sc, bank(ctx, 1), &nbB, adj, 1, bank(ctx, 0), nbA,
                              bank(ctx, 2), nbZ);
   };
@@ -502,6 +576,7 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
   // u = B G p
   auto second_half = [&]() -> int {
     DWA_TRY(applyAd(z, r, w, bank(ctx, 2), &nbZ));
+    if (sm) return launch_vec_update2(ctx, inner, p, z, sc, 1, bank(ctx, 2), nbZ);
     return launch_cg_update2(ctx, inner, p, u, z, sc, adj, 1, bank(ctx, 2), nbZ);
   };
   // between host checks the body (second half of iteration k, first half of k + 1) is
@@ -542,7 +617,7 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
     }
     if (update) {
       // x += scale * x_l (FP64), x_l = 0; true residual; r_l = r / |r|
-      DWA_TRY(launch_fold_acc(ctx, xprec, x, xl, n, scale));
+      DWA_TRY(fold_inner(ctx, inner, x, xl, scale));
       DWA_TRY(true_residual64(ctx, x, rhs, bnorm, &rel, W[W_RES], adj));
       ndbb += 1;
       ++outer;
@@ -567,8 +642,8 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
         DWA_TRY(launch_axpby(ctx, inner, p, f, p, 0.0, n));
         DWA_TRY(launch_scale_gamma(ctx, sc, f * f));
         scale = new_scale;
-        DWA_TRY(launch_convert(ctx, inner, r, DWA_F64, W[W_RES], n, 1.0 / scale));
-        DWA_TRY(launch_smix(ctx, inner, mixAd, w, r, nullptr, 0.0, ctx->Ls, nullptr, nullptr));
+        DWA_TRY(to_inner(ctx, inner, r, W[W_RES], 1.0 / scale));
+        DWA_TRY(premix(mixAd, w, r));
         // (|r_l|^2 is not needed here: the next update 1 sums it before any check)
         rmax = 1.0;
       }
@@ -583,18 +658,62 @@ int reliable_solve(dwa_ctx* ctx, int inner, void* x, const void* rhs, const dwa_
   return status;
 }
 
+// The wave hop's matrices (WaveTable) from the site-local ones: with premix P and output
+// matrix M, chirality c takes M_c P_c on the hop's unit part and M_c P_(1-c) on its gamma
+// part, whose input has the other chirality; -1/4 of the second hops folded in.
+std::vector<double> wave_tables(int Ls, const std::vector<double>& mix) {
+  std::vector<double> out(size_t(WT_COUNT) * 2 * 512, 0.0);
+  if (Ls > kWaveMaxLs) return out;
+  auto M = [&](int kind, int ch) { return &mix[(size_t(kind) * 2 + ch) * Ls * Ls]; };
+  auto put = [&](int table, int part, int ch, const std::vector<double>& m) {
+    double* t = &out[((size_t(table) * 2 + part) * 2 + ch) * 256];
+    for (int lane = 0; lane < 64; ++lane)
+      for (int i = 0; i < 4; ++i) {
+        const int r = lane % 16, k = 4 * (lane / 16) + i;
+        if (r < Ls && k < Ls) t[lane * 4 + i] = m[size_t(r) * Ls + k];
+      }
+  };
+  auto mul = [&](const double* a, const double* b) {
+    std::vector<double> r(size_t(Ls) * Ls, 0.0);
+    for (int i = 0; i < Ls; ++i)
+      for (int j = 0; j < Ls; ++j) {
+        long double acc = 0.0L;
+        for (int k = 0; k < Ls; ++k) acc += (long double)a[i * Ls + k] * b[k * Ls + j];
+        r[size_t(i) * Ls + j] = (double)acc;
+      }
+    return r;
+  };
+  for (int ch = 0; ch < 2; ++ch)
+    for (int part = 0; part < 2; ++part) {
+      const int in = part ? 1 - ch : ch;
+      put(WT_DBB1, part, ch, mul(M(MIX_N, ch), M(MIX_BG, in)));
+      put(WT_DAG1, part, ch, mul(M(MIX_NT, ch), M(MIX_G5_IINVT_GINV, in)));
+      std::vector<double> a(M(MIX_GINV_IINV, ch), M(MIX_GINV_IINV, ch) + size_t(Ls) * Ls);
+      std::vector<double> b(M(MIX_G_BT_G5, ch), M(MIX_G_BT_G5, ch) + size_t(Ls) * Ls);
+      for (auto& v : a) v *= -0.25;
+      for (auto& v : b) v *= -0.25;
+      put(WT_DBB2, part, ch, a);
+      put(WT_DAG2, part, ch, b);
+    }
+  return out;
+}
+
 // Upload the site-local matrices and sweep tables of the context's parameters
 // (allocating the device tables on first use; their sizes depend on Ls only).
 int upload_smatrices(dwa_ctx* ctx, const std::vector<double>& mix, const SweepTables& sweeps,
                      bool alloc) {
   std::vector<float> mix32(mix.begin(), mix.end());
   std::vector<float> sw32(sweeps.coef.begin(), sweeps.coef.end());
+  const std::vector<double> wave = wave_tables(ctx->Ls, mix);
+  const std::vector<float> wave32(wave.begin(), wave.end());
   if (alloc) {
     DWA_HIP(hipMalloc(&ctx->d_mix64, sizeof(double) * mix.size()), "alloc mix");
     DWA_HIP(hipMalloc(&ctx->d_mix32, sizeof(float) * mix.size()), "alloc mix32");
     DWA_HIP(hipMalloc(&ctx->d_sweep_meta, sizeof(int) * sweeps.meta.size()), "alloc sweep meta");
     DWA_HIP(hipMalloc(&ctx->d_sweep64, sizeof(double) * sweeps.coef.size()), "alloc sweep64");
     DWA_HIP(hipMalloc(&ctx->d_sweep32, sizeof(float) * sw32.size()), "alloc sweep32");
+    DWA_HIP(hipMalloc(&ctx->d_wave64, sizeof(double) * wave.size()), "alloc wave tables");
+    DWA_HIP(hipMalloc(&ctx->d_wave32, sizeof(float) * wave.size()), "alloc wave tables");
   }
   DWA_HIP(hipMemcpy(ctx->d_mix64, mix.data(), sizeof(double) * mix.size(), hipMemcpyHostToDevice), "upload mix");
   DWA_HIP(hipMemcpy(ctx->d_mix32, mix32.data(), sizeof(float) * mix32.size(), hipMemcpyHostToDevice), "upload mix32");
@@ -603,6 +722,8 @@ int upload_smatrices(dwa_ctx* ctx, const std::vector<double>& mix, const SweepTa
   DWA_HIP(hipMemcpy(ctx->d_sweep64, sweeps.coef.data(), sizeof(double) * sweeps.coef.size(), hipMemcpyHostToDevice),
           "upload sweep64");
   DWA_HIP(hipMemcpy(ctx->d_sweep32, sw32.data(), sizeof(float) * sw32.size(), hipMemcpyHostToDevice), "upload sweep32");
+  DWA_HIP(hipMemcpy(ctx->d_wave64, wave.data(), sizeof(double) * wave.size(), hipMemcpyHostToDevice), "upload wave");
+  DWA_HIP(hipMemcpy(ctx->d_wave32, wave32.data(), sizeof(float) * wave.size(), hipMemcpyHostToDevice), "upload wave32");
   ctx->h_mix = mix;
   ctx->sweep_meta_host = sweeps.meta;
   ctx->dense_mix = std::getenv("DWA_DENSE_MIX") != nullptr;
@@ -653,6 +774,7 @@ struct BatchSys {
   int nr = 0;
   int prec = DWA_F64;
   void* x = nullptr;          // solution (storage xacc_prec(prec))
+  void* x_out = nullptr;      // where an FP64 solution ends
   const void* rhs = nullptr;  // right-hand sides
   void *r = nullptr, *p = nullptr, *z = nullptr, *q = nullptr, *w = nullptr, *u = nullptr,
        *t = nullptr;
@@ -700,6 +822,14 @@ int batch_first_half(BatchSys& b) {
   dwa_ctx* ctx = b.ctx;
   DevScalars* sc = ctx->batch.d_scal;
   int nbA = 0, nbB = 0;
+  if (use_wave(ctx, b.prec)) {
+    DWA_TRY(wave_dbb(ctx, b.prec, false, b.q, b.p, b.t, bbank(ctx, 0), &nbA, b.nr));
+    DWA_TRY(launch_vec_update1(ctx, b.prec, b.x, b.r, b.p, b.q, sc, bbank(ctx, 1), &nbB, b.nr, bbank(ctx, 0), nbA,
+                               bbank(ctx, 2), b.nb_z));
+    b.nb_r = nbB;
+    b.n_dbb += b.nr;
+    return DWA_OK;
+  }
   DWA_TRY(dbb_from_premix(ctx, b.prec, b.q, b.p, b.u, b.t, bbank(ctx, 0), &nbA, b.nr));
   // a = gamma / |q|^2 per field is summed inside update 1 from the hop's partials
   DWA_TRY(launch_cg_update1(ctx, b.prec, b.x, b.r, b.w, b.p, b.q, sc, bbank(ctx, 1), &nbB, false, b.nr,
@@ -713,6 +843,13 @@ int batch_second_half(BatchSys& b) {
   dwa_ctx* ctx = b.ctx;
   DevScalars* sc = ctx->batch.d_scal;
   int nbZ = 0;
+  if (use_wave(ctx, b.prec)) {
+    DWA_TRY(wave_dbb(ctx, b.prec, true, b.z, b.r, b.t, bbank(ctx, 2), &nbZ, b.nr));
+    b.nb_z = nbZ;
+    DWA_TRY(launch_vec_update2(ctx, b.prec, b.p, b.z, sc, b.nr, bbank(ctx, 2), nbZ));
+    b.n_dbb += b.nr;
+    return DWA_OK;
+  }
   DWA_TRY(dbbdag_from_premix(ctx, b.prec, b.z, b.r, b.w, b.t, bbank(ctx, 2), &nbZ, b.nr));
   b.nb_z = nbZ;
   DWA_TRY(launch_cg_update2(ctx, b.prec, b.p, b.u, b.z, sc, false, b.nr, bbank(ctx, 2), nbZ));
@@ -752,15 +889,25 @@ int cgls_multi(std::vector<BatchSys>& S, hipStream_t st, int maxiter, int check_
     b.iters.assign(b.nr, 0);
     b.converged.assign(b.nr, 0);
     b.breakdown.assign(b.nr, 0);
+    // site-major fields and wave hops as in cgls: a low-precision right-hand side is
+    // site-major already, an FP64 solution is held in u until the end
+    const bool sm = use_wave(ctx, b.prec);
+    b.x_out = b.x;
+    if (sm && b.prec == DWA_F64) b.x = b.u;
     DWA_TRY(launch_zero(ctx, xacc_prec(b.prec), b.x, n, b.nr));
-    DWA_TRY(launch_axpby(ctx, b.prec, b.r, 1.0, b.rhs, 0.0, n, b.nr));
-    DWA_TRY(launch_smix(ctx, b.prec, MIX_G5_IINVT_GINV, b.w, b.r, nullptr, 0.0, ctx->Ls, nullptr, nullptr, b.nr));
-    DWA_TRY(dbbdag_from_premix(ctx, b.prec, b.z, b.r, b.w, b.t, bbank(ctx, 2), &nbA, b.nr));
+    if (sm && b.prec == DWA_F64) DWA_TRY(launch_to_sm(ctx, b.prec, b.r, b.prec, b.rhs, 1.0, b.nr));
+    else DWA_TRY(launch_axpby(ctx, b.prec, b.r, 1.0, b.rhs, 0.0, n, b.nr));
+    if (sm) {
+      DWA_TRY(wave_dbb(ctx, b.prec, true, b.z, b.r, b.t, bbank(ctx, 2), &nbA, b.nr));
+    } else {
+      DWA_TRY(launch_smix(ctx, b.prec, MIX_G5_IINVT_GINV, b.w, b.r, nullptr, 0.0, ctx->Ls, nullptr, nullptr, b.nr));
+      DWA_TRY(dbbdag_from_premix(ctx, b.prec, b.z, b.r, b.w, b.t, bbank(ctx, 2), &nbA, b.nr));
+    }
     b.nb_z = nbA;
     DWA_TRY(launch_norm2(ctx, b.prec, b.rhs, n, bbank(ctx, 1), &nbB, b.nr));
     DWA_TRY(launch_cg_finalize(ctx, 2, sc, bbank(ctx, 2), nbA, bbank(ctx, 1), nbB, b.nr));
     DWA_TRY(launch_axpby(ctx, b.prec, b.p, 1.0, b.z, 0.0, n, b.nr));
-    DWA_TRY(launch_smix(ctx, b.prec, MIX_BG, b.u, b.p, nullptr, 0.0, ctx->Ls, nullptr, nullptr, b.nr));
+    if (!sm) DWA_TRY(launch_smix(ctx, b.prec, MIX_BG, b.u, b.p, nullptr, 0.0, ctx->Ls, nullptr, nullptr, b.nr));
     b.n_dbb = b.nr;
     for (int k = 0; k < b.nr; ++k) {
       ctx->batch.h_active[k] = 1;
@@ -901,6 +1048,8 @@ int cgls_multi(std::vector<BatchSys>& S, hipStream_t st, int maxiter, int check_
     for (int f = 0; f < b.nr; ++f)
       if (b.ctx->batch.h_active[f]) b.iters[f] = k;  // stopped by maxiter
   cleanup();
+  for (auto& b : S)
+    if (use_wave(b.ctx, b.prec) && b.prec == DWA_F64) DWA_TRY(launch_from_sm(b.ctx, b.prec, b.x_out, b.x, b.nr));
   return DWA_OK;
 }
 
@@ -1025,7 +1174,7 @@ int multi_solve(dwa_ctx* const* ctxs, int nctx, const int* nrhs, const dwa_solve
       }
       batch_sys_vectors(S[i]);
       DWA_HIP(hipMemcpyAsync(w.d_coef, w.h_coef, sizeof(double) * nr, hipMemcpyHostToDevice, st), "coef upload");
-      DWA_TRY(launch_convert(ctx, inner, w.lo[inner][BL_RHS], DWA_F64, w.f64[B_PHI], n, 0.0, nr, w.d_coef));
+      DWA_TRY(to_inner(ctx, inner, w.lo[inner][BL_RHS], w.f64[B_PHI], 0.0, nr, w.d_coef));
       // the pinned coefficients are rewritten below only after a synchronisation
       DWA_HIP(hipStreamSynchronize(st), "coef sync");
     }
@@ -1049,7 +1198,7 @@ int multi_solve(dwa_ctx* const* ctxs, int nctx, const int* nrhs, const dwa_solve
         w.h_coef[f] = live[f] ? scale[i][f] : 0.0;
       }
       DWA_HIP(hipMemcpyAsync(w.d_coef, w.h_coef, sizeof(double) * nr, hipMemcpyHostToDevice, st), "coef upload");
-      DWA_TRY(launch_fold_acc(ctx, xacc_prec(inner), w.f64[B_X], w.xacc, n, 0.0, nr, w.d_coef));
+      DWA_TRY(fold_inner(ctx, inner, w.f64[B_X], w.xacc, 0.0, nr, w.d_coef));
       std::vector<double> r2(nr);
       DWA_TRY(batch_true_residual(ctx, nr, st, r2.data()));  // synchronises
       std::vector<double> fac(nr, 1.0);
@@ -1089,8 +1238,9 @@ int multi_solve(dwa_ctx* const* ctxs, int nctx, const int* nrhs, const dwa_solve
               "coef upload");
       DWA_TRY(launch_axpby(ctx, inner, b.p, 1.0, b.p, 0.0, n, nr, w.d_coef));
       DWA_TRY(launch_scale_gamma(ctx, w.d_scal, 1.0, nr, w.d_coef + 2 * nr));
-      DWA_TRY(launch_convert(ctx, inner, b.r, DWA_F64, w.f64[B_RES], n, 0.0, nr, w.d_coef + 3 * nr));
-      DWA_TRY(launch_smix(ctx, inner, MIX_G5_IINVT_GINV, b.w, b.r, nullptr, 0.0, ctx->Ls, nullptr, nullptr, nr));
+      DWA_TRY(to_inner(ctx, inner, b.r, w.f64[B_RES], 0.0, nr, w.d_coef + 3 * nr));
+      if (!use_wave(ctx, inner))
+        DWA_TRY(launch_smix(ctx, inner, MIX_G5_IINVT_GINV, b.w, b.r, nullptr, 0.0, ctx->Ls, nullptr, nullptr, nr));
       DWA_HIP(hipStreamSynchronize(st), "coef sync");
       return DWA_OK;
     };
@@ -1141,7 +1291,7 @@ int multi_solve(dwa_ctx* const* ctxs, int nctx, const int* nrhs, const dwa_solve
         if (!live_any) continue;
         // right-hand sides r / |r| in the inner storage precision
         DWA_HIP(hipMemcpyAsync(w.d_coef, w.h_coef, sizeof(double) * nr, hipMemcpyHostToDevice, st), "coef upload");
-        DWA_TRY(launch_convert(ctx, inner, w.lo[inner][BL_RHS], DWA_F64, w.f64[B_RES], n, 0.0, nr, w.d_coef));
+        DWA_TRY(to_inner(ctx, inner, w.lo[inner][BL_RHS], w.f64[B_RES], 0.0, nr, w.d_coef));
         S.push_back(std::move(b));
         which.push_back(i);
       }
@@ -1165,7 +1315,7 @@ int multi_solve(dwa_ctx* const* ctxs, int nctx, const int* nrhs, const dwa_solve
         }
         // X += |r| e in FP64, then the new residuals
         DWA_HIP(hipMemcpyAsync(w.d_coef, w.h_coef, sizeof(double) * nr, hipMemcpyHostToDevice, st), "coef upload");
-        DWA_TRY(launch_fold_acc(ctx, xacc_prec(inner), w.f64[B_X], w.xacc, n, 0.0, nr, w.d_coef));
+        DWA_TRY(fold_inner(ctx, inner, w.f64[B_X], w.xacc, 0.0, nr, w.d_coef));
         std::vector<double> r2(nr);
         DWA_TRY(batch_true_residual(ctx, nr, st, r2.data()));
         for (int f = 0; f < nr; ++f) {
@@ -1339,6 +1489,14 @@ int dwa_create(dwa_ctx** out, const dwa_params* p, void* stream) {
         lds > 0)
       ctx->max_lds = size_t(lds);
   }
+  // the wave hop's walk: n / d = mulhi(n, floor(2^32 / d) + 1) is exact while n d < 2^32
+  {
+    auto magic = [](long long d) { return d > 1 ? unsigned((1ULL << 32) / (unsigned long long)d + 1) : 0u; };
+    ctx->wgeo = WaveGeo{unsigned(Lx / 2), unsigned(Ly), unsigned(Lz), unsigned(Lt), unsigned(Lz),
+                        magic(Lx / 2), magic(Ly), magic(Lz), magic(Lt)};
+    ctx->wgeo_mzdom = Lz % 8 == 0 ? magic(Lz / 8) : 0u;
+    ctx->wave_geo_ok = Vh * std::max(std::max(Lx, Ly), std::max(Lz, Lt)) < (1LL << 32);
+  }
   // s-matrices
   if ((rc = upload_smatrices(ctx, mix, sweeps, true))) return fail(rc);
   if (const char* e = std::getenv("DWA_HOP_MIN_LDS_KB"))
@@ -1347,6 +1505,11 @@ int dwa_create(dwa_ctx** out, const dwa_params* p, void* stream) {
   const size_t n = field_elems(ctx);
   for (int pr = 0; pr < 3; ++pr)
     if ((rc = hip_fail(hipMalloc(&ctx->prec[pr].links, elem_bytes(pr) * 2 * 4 * 9 * Vh), "alloc links")))
+      return fail(rc);
+  // gathered links where the wave hop can run (also after a change of tuning or alpha)
+  for (int pr = 0; pr < 3; ++pr)
+    if (Vh <= std::max(wave_max_sites(ctx, pr, false), wave_max_sites(ctx, pr, true)) &&
+        (rc = hip_fail(hipMalloc(&ctx->prec[pr].wlinks, elem_bytes(pr) * 2 * 72 * Vh), "alloc links")))
       return fail(rc);
   for (int i = 0; i < W64_COUNT; ++i)
     if ((rc = hip_fail(hipMalloc(&ctx->w64[i], 16 * n), "alloc fp64 workspace"))) return fail(rc);
@@ -1381,7 +1544,12 @@ int dwa_destroy(dwa_ctx* ctx) {
   f(ctx->d_sweep_meta);
   f(ctx->d_sweep64);
   f(ctx->d_sweep32);
-  for (auto& pr : ctx->prec) f(pr.links);
+  f(ctx->d_wave64);
+  f(ctx->d_wave32);
+  for (auto& pr : ctx->prec) {
+    f(pr.links);
+    f(pr.wlinks);
+  }
   for (auto p : ctx->w64) f(p);
   for (auto p : ctx->w32) f(p);
   for (auto p : ctx->w16) f(p);
@@ -1412,7 +1580,10 @@ int dwa_set_alpha(dwa_ctx* ctx, double alpha) {
 int dwa_set_links(dwa_ctx* ctx, const void* U) {
   if (!ctx) return einval("null context");
   if (!U) return einval("null links");
-  for (int pr = 0; pr < 3; ++pr) DWA_TRY(launch_pack_links(ctx, pr, ctx->prec[pr].links, U));
+  for (int pr = 0; pr < 3; ++pr) {
+    DWA_TRY(launch_pack_links(ctx, pr, ctx->prec[pr].links, U));
+    if (ctx->prec[pr].wlinks) DWA_TRY(launch_gather_links(ctx, pr, ctx->prec[pr].wlinks, U));
+  }
   DWA_HIP(hipStreamSynchronize(ctx->stream), "set links sync");
   ctx->links_set = true;
   return DWA_OK;
@@ -1492,8 +1663,12 @@ int dwa_apply_Dbb_batch(dwa_ctx* ctx, int prec, int nrhs, void* out, const void*
   if (!out_norm2) return apply_dbb(ctx, prec, out, in, tb, tr, nrhs);
   // with the per-field |out|^2 from the partial sums of the second hop
   int nb = 0;
-  DWA_TRY(launch_smix(ctx, prec, MIX_BG, tb, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr, nrhs));
-  DWA_TRY(dbb_from_premix(ctx, prec, out, in, tb, tr, bbank(ctx, 0), &nb, nrhs));
+  if (use_wave_soa(ctx, prec, nrhs)) {
+    DWA_TRY(wave_dbb_soa(ctx, prec, false, out, in, tb, tr, nrhs, bbank(ctx, 0), &nb));
+  } else {
+    DWA_TRY(launch_smix(ctx, prec, MIX_BG, tb, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr, nrhs));
+    DWA_TRY(dbb_from_premix(ctx, prec, out, in, tb, tr, bbank(ctx, 0), &nb, nrhs));
+  }
   std::vector<double> h(size_t(nb) * nrhs);
   DWA_HIP(hipMemcpyAsync(h.data(), bbank(ctx, 0), sizeof(double) * h.size(), hipMemcpyDeviceToHost, ctx->stream),
           "norm readback");
@@ -1597,11 +1772,13 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
   }
   auto time_pair = [&](Cand& c, void* x, void* t, void* q) -> int {
     ctx->tune[prec] = c.t;
+    const bool wave = use_wave_soa(ctx, prec, c.nrhs);  // D_bb of this call would run these
     const size_t lds = hop_mix_lds_bytes_host(c.t.ns, Ls, p64 ? 16 : 8, c.nrhs > 1 ? c.t.nf : 1);
-    if (std::max(lds, ctx->hop_min_lds) > ctx->max_lds) return DWA_OK;  // cannot run here
+    if (!wave && std::max(lds, ctx->hop_min_lds) > ctx->max_lds) return DWA_OK;  // cannot run here
     const HopOp ha{x, t, nullptr, nullptr, 1.0, 0.0, 0.0, MIX_N, 1, Ls, nullptr, c.nrhs};
     const HopOp hb{t, q, nullptr, x, -0.25, 0.0, 1.0, MIX_GINV_IINV, 0, Ls, nullptr, c.nrhs};
     auto pair = [&]() -> int {
+      if (wave) return wave_dbb(ctx, prec, false, q, x, t, nullptr, nullptr, c.nrhs);
       DWA_TRY(launch_hop(ctx, prec, ha, nullptr));
       return launch_hop(ctx, prec, hb, nullptr);
     };

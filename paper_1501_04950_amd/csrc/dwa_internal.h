@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <climits>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -202,7 +203,44 @@ struct DevScalars {
 };
 
 struct PrecFields {  // one precision's copy of the links
-  void* links = nullptr;  // [2][4][9][Vh] elems, boundary phase folded
+  void* links = nullptr;   // [2][4][9][Vh] elems, boundary phase folded
+  void* wlinks = nullptr;  // [2][Vh][8][9] elems, gathered per output site (wave hop)
+};
+
+// ----------------------------------------------------------------------------
+// wave-per-site hop (kwave.h)
+struct WaveGeo {  // lattice walk (x/2, y, z in a group of ZB planes, t, group); m*: reciprocals
+  unsigned Lxh, Ly, Lz, Lt, ZB;
+  unsigned mLxh, mLy, mZB, mLt;
+};
+struct FieldStrides {  // elements from one site, slice, spin and colour to the next
+  unsigned site, s, spin, col;
+};
+struct WaveHopArgs {
+  const void* in;
+  void* out;
+  const void* post;
+  const void* links;
+  const void *mixD, *mixT;
+  double* partials;
+  unsigned long long rhs_stride;
+  WaveGeo geo;
+  FieldStrides in_st, post_st, out_st;
+  unsigned Vh, Ls, parity, nrhs, nf;
+  unsigned spw;  // sites of a block per wave
+};
+// The matrix pairs of the four hops of D_bb and D_bb^dag, [WT_COUNT][unit, gamma part][2][64][4]
+// (chirality, lane, step) in the matrix-core operand order, zero beyond L_s.
+enum WaveTable { WT_DBB1 = 0, WT_DBB2, WT_DAG1, WT_DAG2, WT_COUNT };
+struct WaveOp {
+  const void* in;
+  void* out;
+  const void* post;  // WT_DBB2 / WT_DAG2: out = post + M H in
+  int table;
+  int parity_out;
+  double* partials;  // optional |out|^2 partial sums (grouped per field)
+  int nrhs;
+  bool in_soa, post_soa, out_soa;  // else site-major
 };
 
 // FP64 workspace roles (black fields unless noted)
@@ -286,6 +324,11 @@ struct dwa_ctx {
   int* d_sweep_meta = nullptr;     // [MIX_COUNT][2][4]
   double* d_sweep64 = nullptr;     // [MIX_COUNT][2][kMaxStages][4][kLsPad]
   float* d_sweep32 = nullptr;
+  double* d_wave64 = nullptr;      // wave hop tables (WaveTable)
+  float* d_wave32 = nullptr;
+  dwa::WaveGeo wgeo = {};          // wave hop walk; wgeo_mzdom: reciprocal of Lz / 8
+  unsigned wgeo_mzdom = 0;
+  bool wave_geo_ok = false;        // the walk's reciprocals are exact on this lattice
   std::vector<int> sweep_meta_host;
   bool dense_mix = false;          // some sweep program failed its check: dense matrices
   size_t hop_min_lds = 0;          // lower bound on a fused hop block's LDS (limits occupancy)
@@ -319,6 +362,53 @@ inline bool use_dense(const dwa_ctx* ctx, int prec) { return ctx->dense_mix || c
 inline int hop_sites_per_block(const dwa_ctx* ctx, int prec) {
   return hop_specialised(ctx->Ls, use_dense(ctx, prec)) ? ctx->tune[prec].ns : 8;
 }
+
+// Which D_bb and D_bb^dag the wave hop runs: where it is the faster one (16^3 x 32 down to
+// 4^4, all three precisions, one field and twelve).  Not for dense matrices.
+//   L_s without kernels of its own in hop_mix_kernel: always (D_bb of 12^3 x 24, L_s = 10:
+//     FP32 121 -> 86 us, FP64 277 -> 136; L_s = 5: 89 -> 81, 162 -> 121).
+//   L_s = 4, 8, 12, 16 of FP32 and FP64: the smallest lattices only.  Two or four launches
+//     there cost their latency, and a wave's chain of 16 lanes x 4 slices is shorter than a
+//     thread's sweeps (CGLS iteration at 4^3 x 8, L_s = 8: FP64 67 -> 41 us); on a full chip
+//     the sweeps do less work (16^3 x 32, L_s = 16: FP32 hop 97 -> 118 us).
+//   BF16: the matrix cores do the hop as well, so the lines lie higher.
+// Solvers keep their fields site-major (no premixed fields, elementwise updates).  Their rule
+// takes the lattice alone, so that a field of a batch runs the kernels of its own solve, bit
+// for bit; it is set where twelve fields are no slower either (iteration at 1024 sites per
+// parity, L_s = 8, FP32: one field 69 -> 43 us, twelve 120 -> 130; L_s = 12: 72 -> 46, 157
+// -> 140).  D_bb of the caller's SoA fields pays for its relayout and is chosen by all sites
+// of the call.
+constexpr int kWaveMinLs = 2, kWaveMaxLs = 16;
+inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
+  const int Ls = ctx->Ls;
+  if (Ls < kWaveMinLs || Ls > kWaveMaxLs || !ctx->wave_geo_ok) return 0;
+  if (!hop_specialised(Ls, false)) return LLONG_MAX;
+  if (prec == DWA_BF16)
+    return soa ? (Ls >= 12 ? 24576 : (Ls == 8 ? 6144 : 4096)) : (Ls >= 12 ? LLONG_MAX : (Ls == 8 ? 2048 : 1024));
+  return soa ? 1024 : (Ls >= 12 ? 1024 : (Ls == 8 ? 512 : 256));
+}
+inline bool wave_ok(const dwa_ctx* ctx, int prec, bool soa, long long sites) {
+  return sites <= wave_max_sites(ctx, prec, soa) && !use_dense(ctx, prec) && ctx->prec[prec].wlinks;
+}
+inline bool use_wave(const dwa_ctx* ctx, int prec) { return wave_ok(ctx, prec, false, ctx->Vh); }
+inline bool use_wave_soa(const dwa_ctx* ctx, int prec, int nrhs) {
+  return wave_ok(ctx, prec, true, ctx->Vh * (long long)nrhs);
+}
+int launch_wave_hop(dwa_ctx* ctx, int prec, const WaveOp& op, int* nparts);
+int launch_gather_links(dwa_ctx* ctx, int prec, void* dst, const void* src_canon);
+// site-major dst = scale * src (SoA, of the same precision or FP64)
+int launch_to_sm(dwa_ctx* ctx, int prec, void* dst, int prec_in, const void* src, double scale, int nrhs = 1,
+                 const double* scales = nullptr);
+// SoA dst = src (site-major)
+int launch_from_sm(dwa_ctx* ctx, int prec, void* dst, const void* src, int nrhs = 1);
+// FP64 SoA X += scale * x_l and x_l = 0, x_l site-major (FP32)
+int launch_fold_sm(dwa_ctx* ctx, void* X, void* xl, double scale, int nrhs = 1, const double* scales = nullptr);
+// the CGLS updates of site-major fields (no premix: it is part of the wave hop)
+int launch_vec_update1(dwa_ctx* ctx, int prec, void* x, void* r, const void* p, const void* q, DevScalars* s,
+                       double* partials, int* nblocks, int nrhs, const double* qparts, int nq, const double* zparts,
+                       int nz);
+int launch_vec_update2(dwa_ctx* ctx, int prec, void* p, const void* z, DevScalars* s, int nrhs, const double* zparts,
+                       int nz);
 
 // kernel launchers (kernels.hip)
 struct HopOp {
@@ -418,9 +508,20 @@ template <typename S> int pack_links_p(dwa_ctx*, void*, const void*);
 template <typename SO, typename SI> int convert_p(dwa_ctx*, void*, const void*, size_t, double, int,
                                                   const double*);
 
+template <typename S> int launch_wave_hop_p(dwa_ctx*, const WaveOp&, int*);
+template <typename SO, typename SI> int launch_to_sm_p(dwa_ctx*, void*, const void*, double, int, const double*);
+template <typename SO, typename SI, bool ADD>
+int launch_from_sm_p(dwa_ctx*, void*, void*, double, int, const double*);
+template <typename S> int launch_vec_update1_p(dwa_ctx*, void*, void*, const void*, const void*, DevScalars*, double*,
+                                               int*, int, const double*, int, const double*, int);
+template <typename S> int launch_vec_update2_p(dwa_ctx*, void*, const void*, DevScalars*, int, const double*, int);
+template <typename S> int launch_gather_links_p(dwa_ctx*, void*, const void*);
+
 size_t field_elems(const dwa_ctx* ctx);  // Ls * 12 * Vh complex numbers
 void set_error(const std::string& msg);
 int hip_fail(hipError_t e, const char* what);
+// D_bb of nrhs SoA fields with the intermediate half fields tb (black) and tr (red)
+int apply_dbb(dwa_ctx* ctx, int prec, void* out, const void* in, void* tb, void* tr, int nrhs = 1);
 // the static scratch of dwa_apply_Dbb_static (scratch.hip): per-device address lookup
 // (once per device, with that device current) and its size
 int scratch_init(int device);

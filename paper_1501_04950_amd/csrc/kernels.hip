@@ -232,6 +232,41 @@ int launch_hop(dwa_ctx* ctx, int prec, const HopOp& op, int* nblocks_out) {
   }
   DWA_DISPATCH(prec, launch_hop_p<S_>(ctx, op, nblocks_out));
 }
+int launch_wave_hop(dwa_ctx* ctx, int prec, const WaveOp& op, int* nparts) {
+  DWA_DISPATCH(prec, launch_wave_hop_p<S_>(ctx, op, nparts));
+}
+int launch_to_sm(dwa_ctx* ctx, int prec, void* dst, int prec_in, const void* src, double scale, int nrhs,
+                 const double* scales) {
+  if (prec == prec_in) {
+    if (scale != 1.0 || scales) {
+      set_error("relayout of the same precision has no scale");
+      return DWA_EINVAL;
+    }
+    DWA_DISPATCH(prec, (launch_to_sm_p<S_, S_>(ctx, dst, src, scale, nrhs, scales)));
+  }
+  if (prec_in == DWA_F64 && prec == DWA_F32) return launch_to_sm_p<F32, F64>(ctx, dst, src, scale, nrhs, scales);
+  if (prec_in == DWA_F64 && prec == DWA_BF16) return launch_to_sm_p<BF16, F64>(ctx, dst, src, scale, nrhs, scales);
+  set_error("unsupported relayout");
+  return DWA_EINVAL;
+}
+int launch_from_sm(dwa_ctx* ctx, int prec, void* dst, const void* src, int nrhs) {
+  DWA_DISPATCH(prec, (launch_from_sm_p<S_, S_, false>(ctx, dst, const_cast<void*>(src), 1.0, nrhs, nullptr)));
+}
+int launch_fold_sm(dwa_ctx* ctx, void* X, void* xl, double scale, int nrhs, const double* scales) {
+  return launch_from_sm_p<F64, F32, true>(ctx, X, xl, scale, nrhs, scales);
+}
+int launch_vec_update1(dwa_ctx* ctx, int prec, void* x, void* r, const void* p, const void* q, DevScalars* s,
+                       double* partials, int* nblocks, int nrhs, const double* qparts, int nq, const double* zparts,
+                       int nz) {
+  DWA_DISPATCH(prec, launch_vec_update1_p<S_>(ctx, x, r, p, q, s, partials, nblocks, nrhs, qparts, nq, zparts, nz));
+}
+int launch_vec_update2(dwa_ctx* ctx, int prec, void* p, const void* z, DevScalars* s, int nrhs, const double* zparts,
+                       int nz) {
+  DWA_DISPATCH(prec, launch_vec_update2_p<S_>(ctx, p, z, s, nrhs, zparts, nz));
+}
+int launch_gather_links(dwa_ctx* ctx, int prec, void* dst, const void* src) {
+  DWA_DISPATCH(prec, launch_gather_links_p<S_>(ctx, dst, src));
+}
 int launch_smix(dwa_ctx* ctx, int prec, int mix, void* out, const void* in, const void* post,
                 double post_coef, int nslices, double* partials, int* nblocks_out, int nrhs) {
   if (nrhs > 1 && serial("smix")) {

@@ -85,12 +85,7 @@ extern "C" int dwa_apply_Dbb_static(dwa_ctx* ctx, int prec, void* out, const voi
     set_error("static scratch not set up on this device");
     return DWA_EHIP;
   }
-  void* tb = base;                                   // B G in (black)
+  void* tb = base;                                   // B G in, or in site-major (black)
   void* tr = static_cast<unsigned char*>(base) + fb;  // N H_rb B G in (red)
-  int rc = launch_smix(ctx, prec, MIX_BG, tb, in, nullptr, 0.0, ctx->Ls, nullptr, nullptr);
-  if (rc != DWA_OK) return rc;
-  const HopOp a{tb, tr, nullptr, nullptr, 1.0, 0.0, 0.0, MIX_N, 1, ctx->Ls, nullptr, 1};
-  if ((rc = launch_hop(ctx, prec, a, nullptr)) != DWA_OK) return rc;
-  const HopOp b{tr, out, nullptr, in, -0.25, 0.0, 1.0, MIX_GINV_IINV, 0, ctx->Ls, nullptr, 1};
-  return launch_hop(ctx, prec, b, nullptr);
+  return apply_dbb(ctx, prec, out, in, tb, tr);
 }
