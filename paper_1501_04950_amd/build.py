@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 SOURCES = ([f"csrc/kernels_hop_{p}_{ns}.hip" for p in ("f64", "f32", "bf16") for ns in (8, 16, 32)]
            + [f"csrc/kernels_wave_{p}.hip" for p in ("f64", "f32", "bf16")]
            + ["csrc/kernels_f64.hip", "csrc/kernels_f32.hip", "csrc/kernels_bf16.hip",
-              "csrc/kernels.hip", "csrc/adjoint.hip", "csrc/scratch.hip", "csrc/api.cpp",
+              "csrc/kernels.hip", "csrc/dw.hip", "csrc/adjoint.hip", "csrc/scratch.hip", "csrc/api.cpp",
               "csrc/smat.cpp", "csrc/zolotarev.cpp"])
 LIB = os.path.join(PKG, "libdwa.so")
 OBJDIR = os.path.join(PKG, "_build")

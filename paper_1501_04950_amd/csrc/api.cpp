@@ -1623,6 +1623,9 @@ int dwa_apply_Dw(dwa_ctx* ctx, void* out, const void* in, int nslices) {
   if (nslices < 1) return einval("nslices must be >= 1");
   void** W = ctx->w64;
   const size_t vol12 = size_t(ctx->V) * 12;
+  const uintptr_t o = uintptr_t(out), i = uintptr_t(in), bytes = vol12 * 16 * size_t(nslices);
+  if (o + bytes <= i || i + bytes <= o) return launch_dw(ctx, out, in, nslices);
+  // overlapping arrays (up to Ls slices in place): through packed copies
   for (int s0 = 0; s0 < nslices; s0 += ctx->Ls) {
     const int ns = (nslices - s0) < ctx->Ls ? (nslices - s0) : ctx->Ls;
     const double2* src = (const double2*)in + s0 * vol12;

@@ -435,6 +435,8 @@ int launch_pack5(dwa_ctx* ctx, int prec, void* dst_soa, const void* src_canon, i
                  int nslices);
 int launch_unpack5(dwa_ctx* ctx, int prec, void* dst_canon, const void* src_soa, int parity,
                    int nslices);
+// D_w on n canonical FP64 fields (dw.hip)
+int launch_dw(dwa_ctx* ctx, void* out, const void* in, int n);
 int launch_convert(dwa_ctx* ctx, int prec_out, void* out, int prec_in, const void* in, size_t n,
                    double scale, int nrhs = 1, const double* scales = nullptr);
 int launch_zero(dwa_ctx* ctx, int prec, void* p, size_t n, int nrhs = 1);

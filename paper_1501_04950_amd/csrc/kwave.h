@@ -126,6 +126,24 @@ __device__ __forceinline__ R quad_perm(R v) {
   }
 }
 
+// T += gamma_mu x over the four spins of a quad, of which lane g holds spin g.  The factor is
+// the source spin's: x: i (+, +, -, -), y: (-, +, +, -), z: i (+, -, -, +), t: 1.
+template <typename R>
+__device__ __forceinline__ void add_gamma(int mu, int g, const cpx<R>& x, cpx<R>& T) {
+  const R e = mu == 0 ? (g < 2 ? R(1) : R(-1)) : (((g == 0 || g == 3) == (mu == 2)) ? R(1) : R(-1));
+  cpx<R> y;
+  if (mu == 0 || mu == 2) y = cmk<R>(-e * x.im, e * x.re);
+  else if (mu == 1) y = cmk<R>(e * x.re, e * x.im);
+  else y = x;
+  if (mu < 2) {
+    T.re += quad_perm<R, 0x1B>(y.re);
+    T.im += quad_perm<R, 0x1B>(y.im);
+  } else {
+    T.re += quad_perm<R, 0x4E>(y.re);
+    T.im += quad_perm<R, 0x4E>(y.im);
+  }
+}
+
 // rows of the wave's exchange buffer: [24 = colour * 8 + spin * 2 + (re, im)][slice], padded
 template <typename R>
 constexpr int kWavePitch = sizeof(R) == 8 ? 18 : 20;
@@ -186,24 +204,8 @@ __device__ __forceinline__ void wave_hop_valu(const WaveHopArgs& a, __amdgpu_buf
       // the scalar registers hold the links of one or two directions at a time
       if (sizeof(R) == 8 || bwd) __builtin_amdgcn_sched_barrier(0x20);
     }
-    // factor of the source spin's lane: x: i (+, +, -, -), y: (-, +, +, -), z: i (+, -, -, +),
-    // t: 1, the sign being that of spin g here
-    const R e = mu == 0 ? (g < 2 ? R(1) : R(-1)) : (((g == 0 || g == 3) == (mu == 2)) ? R(1) : R(-1));
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const cpx<R> x = v[1][c] - v[0][c];
-      cpx<R> y;
-      if (mu == 0 || mu == 2) y = cmk<R>(-e * x.im, e * x.re);
-      else if (mu == 1) y = cmk<R>(e * x.re, e * x.im);
-      else y = x;
-      if (mu < 2) {
-        T[c].re += quad_perm<R, 0x1B>(y.re);
-        T[c].im += quad_perm<R, 0x1B>(y.im);
-      } else {
-        T[c].re += quad_perm<R, 0x4E>(y.re);
-        T[c].im += quad_perm<R, 0x4E>(y.im);
-      }
-    }
+    for (int c = 0; c < 3; ++c) add_gamma<R>(mu, g, v[1][c] - v[0][c], T[c]);
   }
 }
 
