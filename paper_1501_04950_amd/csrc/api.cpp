@@ -1703,7 +1703,8 @@ int dwa_set_tuning(dwa_ctx* ctx, int prec, int ns, int order, int nf, int dense)
   if (dense != 0 && dense != 1) return einval("dense must be 0 or 1");
   if (!hop_specialised(ctx->Ls, ctx->dense_mix || dense) && ns != 8)
     return einval("the generic hop kernel (this Ls, or dense matrices) runs 8 sites per block");
-  const size_t lds = hop_mix_lds_bytes_host(ns, ctx->Ls, prec == DWA_F64 ? 16 : 8, nf);
+  const int tile = hop_even(ctx->Ls, prec, ctx->dense_mix || dense) ? kEvenTile : ns;
+  const size_t lds = hop_mix_lds_bytes_host(tile, ctx->Ls, prec == DWA_F64 ? 16 : 8, nf);
   if (std::max(lds, ctx->hop_min_lds) > ctx->max_lds) return einval("tile's LDS exceeds the device limit");
   ctx->tune[prec].ns = ns;
   ctx->tune[prec].order = order;
@@ -1776,7 +1777,7 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
   auto time_pair = [&](Cand& c, void* x, void* t, void* q) -> int {
     ctx->tune[prec] = c.t;
     const bool wave = use_wave_soa(ctx, prec, c.nrhs);  // D_bb of this call would run these
-    const size_t lds = hop_mix_lds_bytes_host(c.t.ns, Ls, p64 ? 16 : 8, c.nrhs > 1 ? c.t.nf : 1);
+    const size_t lds = hop_mix_lds_bytes_host(hop_sites_per_block(ctx, prec), Ls, p64 ? 16 : 8, c.nrhs > 1 ? c.t.nf : 1);
     if (!wave && std::max(lds, ctx->hop_min_lds) > ctx->max_lds) return DWA_OK;  // cannot run here
     const HopOp ha{x, t, nullptr, nullptr, 1.0, 0.0, 0.0, MIX_N, 1, Ls, nullptr, c.nrhs};
     const HopOp hb{t, q, nullptr, x, -0.25, 0.0, 1.0, MIX_GINV_IINV, 0, Ls, nullptr, c.nrhs};

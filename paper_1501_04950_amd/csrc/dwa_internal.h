@@ -359,18 +359,27 @@ inline bool hop_specialised(int Ls, bool dense) {
 // Dense fifth-dimension matrices for precision prec: forced for the context (a sweep
 // program failed its check, or DWA_DENSE_MIX) or chosen by the tuning.
 inline bool use_dense(const dwa_ctx* ctx, int prec) { return ctx->dense_mix || ctx->tune[prec].dense; }
+// Ls = 6, 10, 14 of FP64 and FP32 have kernels of one tile size, which no tuning changes: with
+// registers for their slices instead of 32, and 16 sites a block, D_bb of 16^3 x 32 takes 303
+// us in FP64 at Ls = 10 (generic 880; wave per site 488; 8 sites a block 375) and 168 us in
+// FP32 (397; 238; 214).  BF16 runs a wave per site there, and any other Ls the generic kernel.
+constexpr int kEvenTile = 16;
+inline bool hop_even(int Ls, int prec, bool dense) {
+  return !dense && prec != DWA_BF16 && (Ls == 6 || Ls == 10 || Ls == 14);
+}
 inline int hop_sites_per_block(const dwa_ctx* ctx, int prec) {
+  if (hop_even(ctx->Ls, prec, use_dense(ctx, prec))) return kEvenTile;
   return hop_specialised(ctx->Ls, use_dense(ctx, prec)) ? ctx->tune[prec].ns : 8;
 }
 
 // Which D_bb and D_bb^dag the wave hop runs: where it is the faster one (16^3 x 32 down to
 // 4^4, all three precisions, one field and twelve).  Not for dense matrices.
-//   L_s without kernels of its own in hop_mix_kernel: always (D_bb of 12^3 x 24, L_s = 10:
-//     FP32 121 -> 86 us, FP64 277 -> 136; L_s = 5: 89 -> 81, 162 -> 121).
-//   L_s = 4, 8, 12, 16 of FP32 and FP64: the smallest lattices only.  Two or four launches
-//     there cost their latency, and a wave's chain of 16 lanes x 4 slices is shorter than a
-//     thread's sweeps (CGLS iteration at 4^3 x 8, L_s = 8: FP64 67 -> 41 us); on a full chip
-//     the sweeps do less work (16^3 x 32, L_s = 16: FP32 hop 97 -> 118 us).
+//   L_s without kernels of its own in hop_mix_kernel: always (D_bb of 12^3 x 24, L_s = 9:
+//     FP32 117 -> 84 us, FP64 254 -> 132; L_s = 5: 89 -> 81, 162 -> 121).
+//   Other L_s of FP32 and FP64: the smallest lattices only.  Two or four launches there cost
+//     their latency, and a wave's chain of 16 lanes x 4 slices is shorter than a thread's
+//     sweeps (CGLS iteration at 4^3 x 8, L_s = 8: FP64 67 -> 41 us); on a full chip the sweeps
+//     do less work (D_bb of 16^3 x 32, L_s = 10: FP32 168 us against 238).
 //   BF16: the matrix cores do the hop as well, so the lines lie higher.
 // Solvers keep their fields site-major (no premixed fields, elementwise updates).  Their rule
 // takes the lattice alone, so that a field of a batch runs the kernels of its own solve, bit
@@ -382,10 +391,10 @@ constexpr int kWaveMinLs = 2, kWaveMaxLs = 16;
 inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
   const int Ls = ctx->Ls;
   if (Ls < kWaveMinLs || Ls > kWaveMaxLs || !ctx->wave_geo_ok) return 0;
-  if (!hop_specialised(Ls, false)) return LLONG_MAX;
+  if (!hop_specialised(Ls, false) && !hop_even(Ls, prec, false)) return LLONG_MAX;
   if (prec == DWA_BF16)
     return soa ? (Ls >= 12 ? 24576 : (Ls == 8 ? 6144 : 4096)) : (Ls >= 12 ? LLONG_MAX : (Ls == 8 ? 2048 : 1024));
-  return soa ? 1024 : (Ls >= 12 ? 1024 : (Ls == 8 ? 512 : 256));
+  return soa ? 1024 : (Ls >= 10 ? 1024 : (Ls >= 6 ? 512 : 256));
 }
 inline bool wave_ok(const dwa_ctx* ctx, int prec, bool soa, long long sites) {
   return sites <= wave_max_sites(ctx, prec, soa) && !use_dense(ctx, prec) && ctx->prec[prec].wlinks;

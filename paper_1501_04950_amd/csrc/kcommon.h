@@ -1094,8 +1094,11 @@ MixTables mix_tables(dwa_ctx* ctx, int kind) {
   } else {                            \
     switch (Ls) {                     \
       case 4: M(4, false); break;     \
+      case 6: M(6, false); break;     \
       case 8: M(8, false); break;     \
+      case 10: M(10, false); break;   \
       case 12: M(12, false); break;   \
+      case 14: M(14, false); break;   \
       case 16: M(16, false); break;   \
       default: M(0, false); break;    \
     }                                 \

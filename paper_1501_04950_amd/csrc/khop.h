@@ -5,9 +5,10 @@
 
 namespace dwa {
 
-// Ls values with their own compiled kernels; any other Ls <= 32 runs the generic one,
-// which is also the only one compiled with the dense fallback (both with 8 sites per
-// block, so only the 8-site tile carries them).
+// Ls values with their own compiled kernels (4, 8, 12, 16 for every tile; 6, 10, 14 of FP64
+// and FP32 for one); any other Ls <= 32 runs the generic one, which is also the only one
+// compiled with the dense fallback (both with 8 sites per block, so only the 8-site tile
+// carries them).
 template <typename S, int NS, int MODE, int KIND>
 int launch_hop_mix_mk(dwa_ctx* ctx, const HopDev& a, dim3 grid, dim3 block, size_t shm) {
 #define DWA_HOPMIX(LSV, DV)                                                                        \
@@ -31,6 +32,16 @@ int launch_hop_mix_mk(dwa_ctx* ctx, const HopDev& a, dim3 grid, dim3 block, size
     if (dense) DWA_HOPMIX(0, true);
     else DWA_HOPMIX(0, false);
     return DWA_OK;
+  }
+  if constexpr (NS == kEvenTile && S::prec != DWA_BF16) {
+    if (hop_even(ctx->Ls, S::prec, dense)) {
+      switch (ctx->Ls) {
+        case 6: DWA_HOPMIX(6, false); break;
+        case 10: DWA_HOPMIX(10, false); break;
+        default: DWA_HOPMIX(14, false); break;
+      }
+      return DWA_OK;
+    }
   }
 #undef DWA_HOPMIX
   set_error("fused hop: the generic kernels run 8 sites per block");

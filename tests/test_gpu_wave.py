@@ -73,7 +73,7 @@ def test_wave_dbb(dims, Ls, prec):
     assert max(e, ed) < TOL[prec] and max(g, gd) < TOL[prec]
 
     ctx.set_tuning(prec, ns, order, nf, 0)
-    if ctx.Ls in (4, 8, 12, 16):  # larger batches of these run the site-block kernels
+    if Ls in (4, 8, 12, 16) or (Ls in (6, 10, 14) and prec != "bf16"):  # larger batches: site blocks
         ctx.close()
         return
     nbytes = x.numel() * x.element_size()
@@ -120,4 +120,35 @@ def test_wave_solvers(dims, Ls, mode, inner, delta):
         d, db = float(torch.linalg.vector_norm(y - g)) / n, float(torch.linalg.vector_norm(ys[k] - g)) / n
         print(f"    source {k}: {st['iters']} / {sg['iters']} iterations, difference {d:.1e}, batch {db:.1e}", flush=True)
         assert max(d, db) <= 1e-8
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("Ls", [6, 10, 14])
+def test_even_ls_site_blocks(Ls, prec):
+    """L_s = 6, 10, 14 beyond the wave hop's lattices: their site-block kernels (16 sites, the
+    last block partly filled) against the oracle and the dense kernels, every block order
+    and several fields per block bit for bit."""
+    s = Setup((6, 6, 10, 6), Ls)
+    ctx, x = s.ctx, s.pack(prec)
+    print(f"[gpu] site-block D_bb Ls={Ls} {prec}", flush=True)
+    ref, ref_d = s.rb.Dbb(s.x), s.rb.Dbb_dag(s.x)
+    ctx.reserve_batch(3)
+    xs = torch.stack([x * (1 + k) for k in range(3)]).contiguous()
+    first = None
+    for order in ("slab", "lex"):
+        for nf in (1, 2):
+            ctx.set_tuning(prec, 8, order, nf, 0)
+            y, z = ctx.apply_Dbb(x, prec), ctx.apply_Dbb_dag(x, prec)
+            ys = ctx.apply_Dbb_batch(xs, prec)
+            first = first or (y, z, ys)
+            assert all(torch.equal(a, b) for a, b in zip((y, z, ys), first))
+            assert torch.equal(ys[0], y)
+    e, ed = rel(s.full(first[0], prec), ref), rel(s.full(first[1], prec), ref_d)
+    ctx.set_tuning(prec, 8, "slab", 1, 1)
+    g = rel(s.full(ctx.apply_Dbb(x, prec), prec), ref)
+    print(f"    error {e:.2e}, dagger {ed:.2e} (dense {g:.2e})", flush=True)
+    assert max(e, ed, g) < TOL[prec]
+    with pytest.raises(dwa.DwaError):
+        ctx.set_tuning(prec, 16, "slab", 1, 0)
     ctx.close()
