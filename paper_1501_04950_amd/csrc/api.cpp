@@ -1742,6 +1742,7 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
     HopTune t;
     int nrhs;
     double us;
+    double site_us = -1.0;  // by the site-block kernels, where D_bb of one field runs others
   };
   std::vector<Cand> cands;
   const bool spec = hop_specialised(Ls, ctx->dense_mix);
@@ -1774,9 +1775,8 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
     (void)hipEventDestroy(e0);
     return hip_fail(hipErrorOutOfMemory, "event");
   }
-  auto time_pair = [&](Cand& c, void* x, void* t, void* q) -> int {
+  auto time_pair = [&](Cand& c, void* x, void* t, void* q, bool wave) -> int {
     ctx->tune[prec] = c.t;
-    const bool wave = use_wave_soa(ctx, prec, c.nrhs);  // D_bb of this call would run these
     const size_t lds = hop_mix_lds_bytes_host(hop_sites_per_block(ctx, prec), Ls, p64 ? 16 : 8, c.nrhs > 1 ? c.t.nf : 1);
     if (!wave && std::max(lds, ctx->hop_min_lds) > ctx->max_lds) return DWA_OK;  // cannot run here
     const HopOp ha{x, t, nullptr, nullptr, 1.0, 0.0, 0.0, MIX_N, 1, Ls, nullptr, c.nrhs};
@@ -1811,9 +1811,25 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
     void* t = W[p64 ? W_OPR : L_OPR];
     void* q = W[p64 ? W_Q : L_Q];
     if ((rc = launch_zero(ctx, prec, x, n)) == DWA_OK) rc = launch_zero(ctx, prec, t, n);
-    for (size_t k = 0; k < cands.size() && rc == DWA_OK; ++k) rc = time_pair(cands[k], x, t, q);
+    for (size_t k = 0; k < cands.size() && rc == DWA_OK; ++k) rc = time_pair(cands[k], x, t, q, false);
+    // Where D_bb of one field takes the wave hop, every tile of the sweeps stands for its
+    // time (against the dense matrices), and among themselves the tiles are ranked by the
+    // site-block kernels, which larger calls of the context run.
+    ctx->tune[prec] = cands[0].t;
+    if (rc == DWA_OK && use_wave_soa(ctx, prec, 1)) {
+      Cand w{cands[0].t, 1, -1.0};
+      rc = time_pair(w, x, t, q, true);
+      for (auto& c : cands)
+        if (!c.t.dense && c.us >= 0) {
+          c.site_us = c.us;
+          c.us = w.us;
+        }
+    }
   }
   long long best = rc == DWA_OK ? best_of(0) : -1;
+  if (best >= 0 && cands[size_t(best)].site_us >= 0)
+    for (size_t k = 0; k < cands.size(); ++k)
+      if (cands[k].site_us >= 0 && cands[k].site_us < cands[size_t(best)].site_us) best = (long long)k;
   HopTune chosen = best >= 0 ? cands[size_t(best)].t : saved;
   // fields per block, on a batch of up to 12 fields when one is reserved
   const int nb = std::min(ctx->batch.nmax, 12);
@@ -1830,7 +1846,10 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
       c.nf = nf;
       cands.push_back(Cand{c, nb, -1.0});
     }
-    for (size_t k = from; k < cands.size() && rc == DWA_OK; ++k) rc = time_pair(cands[k], x, t, q);
+    for (size_t k = from; k < cands.size() && rc == DWA_OK; ++k) {
+      ctx->tune[prec] = cands[k].t;
+      rc = time_pair(cands[k], x, t, q, use_wave_soa(ctx, prec, nb));
+    }
     const long long bb = rc == DWA_OK ? best_of(from) : -1;
     if (bb >= 0) chosen.nf = cands[size_t(bb)].t.nf;
   }

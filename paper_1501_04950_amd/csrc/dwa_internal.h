@@ -226,7 +226,7 @@ struct WaveHopArgs {
   unsigned long long rhs_stride;
   WaveGeo geo;
   FieldStrides in_st, post_st, out_st;
-  unsigned Vh, Ls, parity, nrhs, nf;
+  unsigned Vh, Ls, parity, nrhs;
   unsigned spw;  // sites of a block per wave
 };
 // The matrix pairs of the four hops of D_bb and D_bb^dag, [WT_COUNT][unit, gamma part][2][64][4]

@@ -161,8 +161,7 @@ __device__ __forceinline__ void wave_hop_valu(const WaveHopArgs& a, __amdgpu_buf
                                               cpx<RealOf<S>> T[3]) {
   using R = RealOf<S>;
   constexpr unsigned E = sizeof(typename S::elem);
-  // opaque, so that the compiler does not move a site's links out of the loop over fields
-  // (144 scalar registers and more)
+  // opaque, so that the links' addresses are not computed ahead and spilled
   unsigned lsite = w.cb;
   asm volatile("" : "+s"(lsite));
   cptr<R> L = as_const(reinterpret_cast<const R*>(a.links) + size_t(lsite) * 144);
@@ -387,8 +386,7 @@ __device__ __forceinline__ void wave_hop_bf16(const uint32_t* tab, const WaveLin
 // than one wave per site was no faster on 4^4 (44 against 42 us) and slower from 8^4 on.
 //   INSM   the input is site-major (BF16 reads four spins at once); else by strides
 //   OUTL   0: by strides; 1: site-major; 2: SoA through an LDS tile of the block's sites
-//   MULTI  several fields per block (nf > 1), which share a site's links
-template <typename S, bool SPLIT, bool POST, bool INSM, int OUTL, bool MULTI>
+template <typename S, bool SPLIT, bool POST, bool INSM, int OUTL>
 __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_kernel(WaveHopArgs a) {
   using R = RealOf<S>;
   using E = typename S::elem;
@@ -399,7 +397,6 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
   __shared__ __align__(16) R xbuf[BF ? 1 : NW][SPLIT ? 2 : 1][BF ? 4 : kWaveBuf<R>];
   __shared__ __align__(16) uint32_t ltab[NW][BF ? 72 * kLinkStep / 4 : 4];
   __shared__ double wsum[NW];
-  __shared__ double fsum[MULTI ? NW : 1][MULTI ? 64 : 1];  // (nf <= 64)
   extern __shared__ __align__(16) char tile_raw[];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kq = lane >> 4;
@@ -424,13 +421,12 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
   const unsigned sc = s < Ls ? s : Ls - 1, cc = c < 3 ? c : 2;  // idle lanes repeat others
   const unsigned post_lane = POST ? (sc * a.post_st.s + cc * a.post_st.col) * EB : 0u;
   const unsigned out_lane = (sc * a.out_st.s + cc * a.out_st.col) * EB;
-  const unsigned f0 = MULTI ? blockIdx.y * a.nf : blockIdx.y;
-  const unsigned f1 = MULTI ? (f0 + a.nf < a.nrhs ? f0 + a.nf : a.nrhs) : f0 + 1;
+  const unsigned f = blockIdx.y;  // field
   const unsigned per = NW * a.spw;  // sites of the block
   const unsigned site0 = xcd_range(blockIdx.x, gridDim.x) * per;
   const unsigned site1 = site0 + per < a.Vh ? site0 + per : a.Vh;
   const unsigned fbytes = 12u * a.Ls * a.Vh * EB;
-  auto field = [&](const void* p, unsigned f) {
+  auto field = [&](const void* p) {
     return make_rsrc(static_cast<const char*>(p) + size_t(f) * a.rhs_stride * EB, fbytes);
   };
   constexpr bool NORM = POST && OUTL != 2;  // (the tiled store serves operators without norms)
@@ -485,21 +481,6 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
       }
     }
   };
-  // several fields per block: |out|^2 per wave and field
-  auto field_norm = [&](unsigned f) {
-    if constexpr (POST && MULTI) {
-      if (a.partials) {
-        const double v = wave_sum(nrm);
-        if (lane == 0) fsum[wid][f - f0] += v;
-        nrm = 0.0;
-      }
-    }
-  };
-  if constexpr (MULTI) {
-    if (a.partials) fsum[wid][lane] = 0.0;
-    wave_lds_sync();
-  }
-
   if constexpr (BF) {
     const WaveLinkLane ll = wave_link_lane(lane);
     unsigned lane_c[3];
@@ -512,69 +493,56 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
     const unsigned cnt = first >= site1 ? 0u : (site1 - first < a.spw ? site1 - first : a.spw);
     if (cnt) {
       const WaveSite row = wave_site(a.geo, first, a.parity);
-      __amdgpu_buffer_rsrc_t ri = field(a.in, f0), rp = field(POST ? a.post : a.in, f0), ro = field(a.out, f0);
+      const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
       uint2 lk = wave_load_links(a, row.cb, lane);
       for (unsigned k = 0; k < cnt; ++k) {
         WaveSite w;
         wave_row_step(a.geo, row, k, w);
-        for (unsigned f = f0; f < f1; ++f) {
-          if constexpr (MULTI) {
-            ri = field(a.in, f);
-            rp = field(POST ? a.post : a.in, f);
-            ro = field(a.out, f);
-          }
-          WaveIn v;
-          wave_load_bf16<INSM>(a, ri, w, lane_c, kq, v);
-          cpx<R> pv[2][2];
-          load_post(rp, w.cb, 0, pv[0]);
-          load_post(rp, w.cb, 1, pv[1]);
-          if (!MULTI || f == f0) {
-            wave_stage_links(ltab[wid], lane, lk);
-            if (k + 1 < cnt) lk = wave_load_links(a, w.cb + 1, lane);
-          }
-          dwa_f4 B0[2], B1[2];
-          wave_hop_bf16<SPLIT>(ltab[wid], ll, v, B0, B1);
-          cpx<R> o[4];
-          mix(0, B0[0], B1[0], pv[0], o);
-          mix(1, B0[1], B1[1], pv[1], o + 2);
-          store(ro, w.cb, wid * a.spw + k, 0, std::integral_constant<int, 4>(), o);
-          field_norm(f);
-        }
+        WaveIn v;
+        wave_load_bf16<INSM>(a, ri, w, lane_c, kq, v);
+        cpx<R> pv[2][2];
+        load_post(rp, w.cb, 0, pv[0]);
+        load_post(rp, w.cb, 1, pv[1]);
+        wave_stage_links(ltab[wid], lane, lk);
+        if (k + 1 < cnt) lk = wave_load_links(a, w.cb + 1, lane);
+        dwa_f4 B0[2], B1[2];
+        wave_hop_bf16<SPLIT>(ltab[wid], ll, v, B0, B1);
+        cpx<R> o[4];
+        mix(0, B0[0], B1[0], pv[0], o);
+        mix(1, B0[1], B1[1], pv[1], o + 2);
+        store(ro, w.cb, wid * a.spw + k, 0, std::integral_constant<int, 4>(), o);
       }
     }
   } else {
     const int s4 = lane >> 2, g = lane & 3;
     const unsigned in_lane = (unsigned(s4 < Ls ? s4 : Ls - 1) * a.in_st.s + unsigned(g) * a.in_st.spin) * EB;
     R* buf = xbuf[wid][0];
+    const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
     for (unsigned k = 0; k < a.spw; ++k) {
       const unsigned idx = site0 + k * NW + wid;
       if (idx >= site1) break;
       const WaveSite w = wave_site(a.geo, idx, a.parity);
-      for (unsigned f = f0; f < f1; ++f) {
-        const __amdgpu_buffer_rsrc_t ri = field(a.in, f), rp = field(POST ? a.post : a.in, f), ro = field(a.out, f);
-        cpx<R> pv[2][2];
-        load_post(rp, w.cb, 0, pv[0]);
-        load_post(rp, w.cb, 1, pv[1]);
-        cpx<R> D[3], T[3];
-        wave_hop_valu<S>(a, ri, w, in_lane, g, D, T);
-        if constexpr (!SPLIT) {
+      cpx<R> pv[2][2];
+      load_post(rp, w.cb, 0, pv[0]);
+      load_post(rp, w.cb, 1, pv[1]);
+      cpx<R> D[3], T[3];
+      wave_hop_valu<S>(a, ri, w, in_lane, g, D, T);
+      if constexpr (!SPLIT) {
 #pragma unroll
-          for (int k = 0; k < 3; ++k) D[k] = D[k] + T[k];
-        }
-        wave_lds_sync();
-        wave_put<R>(buf, s4, g, D);
-        if constexpr (SPLIT) wave_put<R>(xbuf[wid][SPLIT ? 1 : 0], s4, g, T);
-        wave_lds_sync();
+        for (int k = 0; k < 3; ++k) D[k] = D[k] + T[k];
+      }
+      wave_lds_sync();
+      wave_put<R>(buf, s4, g, D);
+      if constexpr (SPLIT) wave_put<R>(xbuf[wid][SPLIT ? 1 : 0], s4, g, T);
+      wave_lds_sync();
 #pragma unroll
-        for (int ch = 0; ch < 2; ++ch) {
-          const acc4<M> B0 = wave_get<M>(buf, lane, ch);
-          acc4<M> B1 = B0;
-          if constexpr (SPLIT) B1 = wave_get<M>(buf + kWaveBuf<R>, lane, ch);
-          cpx<R> o[2];
-          mix(ch, B0, B1, pv[ch], o);
-          store(ro, w.cb, idx - site0, 2 * ch, std::integral_constant<int, 2>(), o);
-        }
-        field_norm(f);
+      for (int ch = 0; ch < 2; ++ch) {
+        const acc4<M> B0 = wave_get<M>(buf, lane, ch);
+        acc4<M> B1 = B0;
+        if constexpr (SPLIT) B1 = wave_get<M>(buf + kWaveBuf<R>, lane, ch);
+        cpx<R> o[2];
+        mix(ch, B0, B1, pv[ch], o);
+        store(ro, w.cb, idx - site0, 2 * ch, std::integral_constant<int, 2>(), o);
       }
     }
   }
@@ -584,24 +552,13 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
     __syncthreads();
     const E* tile = reinterpret_cast<const E*>(tile_raw);
     const WaveSite w0 = wave_site(a.geo, site0, a.parity);
-    E* out = reinterpret_cast<E*>(a.out) + size_t(f0) * a.rhs_stride;
+    E* out = reinterpret_cast<E*>(a.out) + size_t(f) * a.rhs_stride;
     for (int t = threadIdx.x; t < 12 * Ls * NSB; t += NW * 64) {
       const int row = t / NSB, j = t % NSB;
       if (site0 + j < site1) out[size_t(row) * a.Vh + w0.cb + j] = tile[row * (NSB + 1) + j];
     }
   }
-  if constexpr (POST && MULTI) {
-    if (a.partials) {
-      __syncthreads();
-      const unsigned f = f0 + threadIdx.x;
-      if (f < f1) {
-        double t = 0.0;
-        for (int i = 0; i < NW; ++i) t += fsum[i][threadIdx.x];
-        a.partials[size_t(f) * gridDim.x + blockIdx.x] = t;
-      }
-    }
-  }
-  if constexpr (POST && !MULTI) {
+  if constexpr (POST) {
     if (a.partials) {
       nrm = wave_sum(nrm);
       if (lane == 0) wsum[wid] = nrm;
@@ -916,9 +873,10 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
     a.geo.ZB = ctx->wgeo.ZB;
     a.geo.mZB = ctx->wgeo.mZB;
   }
-  const unsigned nf_t = ctx->tune[S::prec].nf > 1 ? (unsigned)ctx->tune[S::prec].nf : 1u;
-  a.nf = (op.nrhs > 1 && !tile) ? (nf_t < a.nrhs ? nf_t : a.nrhs) : 1u;
-  const unsigned ny = (a.nrhs + a.nf - 1) / a.nf;
+  // one field per block: with the links of a site shared by several, a block's fields run one
+  // after the other (BF16 iteration of 12 fields of 12^3 x 24, L_s = 12: 1194 us; two fields a
+  // block 1554, twelve 1359)
+  const unsigned ny = a.nrhs;
   constexpr unsigned NW = 4;  // waves of a block
   // Sites per wave.  BF16: consecutive ones of an x row, whose links are loaded a site ahead,
   // while enough waves are left to fill the 256 CUs; the tiled store wants 128-byte rows (32
@@ -938,13 +896,8 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
   const dim3 grid(nblk, ny);
   const size_t shm = tile ? size_t(12) * a.Ls * (NSB + 1) * EB : 0;
   if (nparts) *nparts = int(nblk);
-#define DWA_WAVE_M(SPLIT, POST, INSM, OUTL, MULTI)                                                     \
-  hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL, MULTI>), grid, dim3(256), shm, ctx->stream, a)
-#define DWA_WAVE(SPLIT, POST, INSM, OUTL)                         \
-  do {                                                            \
-    if (a.nf > 1) DWA_WAVE_M(SPLIT, POST, INSM, OUTL, true);      \
-    else DWA_WAVE_M(SPLIT, POST, INSM, OUTL, false);              \
-  } while (0)
+#define DWA_WAVE(SPLIT, POST, INSM, OUTL) \
+  hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL>), grid, dim3(256), shm, ctx->stream, a)
   if (split) {
     if (op.post || op.out_soa) {
       set_error("wave hop: unsupported combination");
@@ -957,13 +910,11 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
       set_error("wave hop: unsupported combination");
       return DWA_EINVAL;
     }
-    if (tile)
-      DWA_WAVE_M(false, true, true, 2, false);
+    if (tile) DWA_WAVE(false, true, true, 2);
     else if (op.out_soa) DWA_WAVE(false, true, true, 0);
     else DWA_WAVE(false, true, true, 1);
   }
 #undef DWA_WAVE
-#undef DWA_WAVE_M
   return hip_fail(hipGetLastError(), "wave hop launch");
 }
 
