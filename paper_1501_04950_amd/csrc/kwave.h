@@ -372,12 +372,13 @@ __device__ __forceinline__ void wave_hop_bf16(const uint32_t* tab, const WaveLin
 // output matrix M, chirality c takes M_c P_c on D and M_c P_(1-c) on T (SPLIT; otherwise one
 // matrix serves both parts and they are summed first).
 //
-// What bounds it.  BF16 on a full chip (16^3 x 32, L_s = 16): issue, not memory - 19 us of
-// bytes at 5.2 TB/s; the matrix instructions (24 of the hop, 32 of the mix) and the gather and
-// staging around them take 37 us (first hop) and 42 us (second, which adds the x term and the
-// norm), against 47 + 20 us of hop_mix_kernel and its premix pass.  No persistent grid (50 us),
-// no double-buffered neighbours (46 us: the registers cost a wave per SIMD), no three-way BF16
-// split of the mix (44 us).  Five waves per SIMD; six spill (72 us).
+// What bounds it.  BF16 on a full chip (16^3 x 32, L_s = 16): issue, not memory - 26 and 36 us
+// of bytes at 5.2 TB/s (138 and 188 MB); 28 matrix instructions a site in the first hop (12 of
+// the hop, 16 of the mix) and 20 in the second, and 101 and 135 vector ones for gathers,
+// staging, x term and norm, take 36 and 39 us, against 47 us and a premix pass of 20 us of
+// hop_mix_kernel.  Not kept: a persistent grid (50 us where this took 46), double-buffered
+// neighbours (46: the registers cost a wave per SIMD), a three-way BF16 split of the mix (44
+// against 44).  Five waves per SIMD; six spill (72 us).
 // FP64 / FP32: on small lattices the latency of one site's chain - two hops and two updates of
 // a CGLS iteration on 4^4, L_s = 8, FP64 go from 71 to 44 us, D_bb from 29 to 18 - and on a
 // full chip the vector unit, which multiplies both spins of a chirality where the half-spinor
