@@ -380,7 +380,10 @@ inline int hop_sites_per_block(const dwa_ctx* ctx, int prec) {
 //     their latency, and a wave's chain of 16 lanes x 4 slices is shorter than a thread's
 //     sweeps (CGLS iteration at 4^3 x 8, L_s = 8: FP64 67 -> 41 us); on a full chip the sweeps
 //     do less work (D_bb of 16^3 x 32, L_s = 10: FP32 168 us against 238).
-//   BF16: the matrix cores do the hop as well, so the lines lie higher.
+//   BF16: the matrix cores do the hop as well, so the lines lie higher.  D_bb at L_s >= 12:
+//     while the input, its site-major copy, the red field and the output fit the 256 MB
+//     Infinity Cache (16^3 x 32, L_s = 16, one field 111 -> 103 us, L_s = 12 97 -> 89; two
+//     fields 233 against 238; twelve of 12^3 x 24, L_s = 12 389 against 414).
 // Solvers keep their fields site-major (no premixed fields, elementwise updates).  Their rule
 // takes the lattice alone, so that a field of a batch runs the kernels of its own solve, bit
 // for bit; it is set where twelve fields are no slower either (iteration at 1024 sites per
@@ -393,7 +396,7 @@ inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
   if (Ls < kWaveMinLs || Ls > kWaveMaxLs || !ctx->wave_geo_ok) return 0;
   if (!hop_specialised(Ls, false) && !hop_even(Ls, prec, false)) return LLONG_MAX;
   if (prec == DWA_BF16)
-    return soa ? (Ls >= 12 ? 24576 : (Ls == 8 ? 6144 : 4096)) : (Ls >= 12 ? LLONG_MAX : (Ls == 8 ? 2048 : 1024));
+    return soa ? (Ls >= 12 ? (1LL << 28) / (4 * 48 * Ls) : (Ls == 8 ? 6144 : 4096)) : (Ls >= 12 ? LLONG_MAX : (Ls == 8 ? 2048 : 1024));
   return soa ? 1024 : (Ls >= 10 ? 1024 : (Ls >= 6 ? 512 : 256));
 }
 inline bool wave_ok(const dwa_ctx* ctx, int prec, bool soa, long long sites) {
