@@ -179,14 +179,15 @@ int dwa_apply_Dbb_static(dwa_ctx *ctx, int prec, void *out_b, const void *in_b);
  * on every slice, and M_kind is a fifth-dimension matrix of dwa_debug_smatrix (kinds
  * 0..6; 0 = identity runs the hop alone).  D_bb is built from two such launches
  * (kinds 2 and 3) and D_bb^dag from kinds 5 and 6, except where a hop with one wavefront
- * per site is the faster one (small lattices, BF16, and the Ls between 2 and 16 other than
- * 4, 8, 12, 16), which applies the same matrices in another order.  Half fields of precision prec;
+ * per site is the faster one (small lattices, many BF16 calls, and odd Ls up to 15), which
+ * applies the same matrices in another order.  Half fields of precision prec;
  * out and in must not overlap.  Exposed for measurement and tests. */
 int dwa_apply_hop(dwa_ctx *ctx, int prec, int parity_out, int kind, void *out, const void *in);
 
 /* Tiles and block traversal of the fused hop.  A block of the hop kernel computes ns
  * consecutive checkerboard sites on all Ls slices (ns = 8, 16 or 32; Ls = 4, 8, 12, 16
- * have kernels for all three, any other Ls and the dense fallback run 8), and blocks
+ * have kernels for all three; any other Ls and the dense fallback have one tile, named 8,
+ * which for Ls = 6, 10, 14 in FP64 and FP32 is one of 16 sites), and blocks
  * walk the lattice in one of three orders: 0 = t-slabs (default), 1 = checkerboard
  * order, 2 = z-planes per XCD.  Only the assignment of sites to blocks changes: every
  * site's arithmetic is the same, so D_bb and every hop output are bitwise identical
