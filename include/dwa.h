@@ -229,8 +229,9 @@ int dwa_autotune(dwa_ctx *ctx, int prec, int reps, dwa_tune_entry *entries, int 
  * every precision-specific launch (hop, site-local mixes, CG updates).  dwa_set_tuning
  * rejects a tile other than 8, 16, 32, an order outside 0..2, nf outside 1..64, dense
  * other than 0 / 1, a tile other than 8 where the generic kernel runs, and a
- * configuration whose LDS exceeds the device limit (DWA_EINVAL).  Output pointers of
- * dwa_get_tuning may be NULL. */
+ * configuration whose LDS exceeds the device limit (DWA_EINVAL).  dwa_get_tuning reports
+ * what dwa_set_tuning takes (ns = 8 where there is one tile); its output pointers may be
+ * NULL. */
 int dwa_set_tuning(dwa_ctx *ctx, int prec, int ns, int order, int nf, int dense);
 int dwa_get_tuning(const dwa_ctx *ctx, int prec, int *ns, int *order, int *nf, int *dense);
 

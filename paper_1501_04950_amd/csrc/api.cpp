@@ -1716,7 +1716,8 @@ int dwa_set_tuning(dwa_ctx* ctx, int prec, int ns, int order, int nf, int dense)
 int dwa_get_tuning(const dwa_ctx* ctx, int prec, int* ns, int* order, int* nf, int* dense) {
   if (!ctx) return einval("null context");
   if (!valid_prec(prec)) return einval("bad precision");
-  if (ns) *ns = hop_sites_per_block(ctx, prec);
+  // the tile's name in dwa_set_tuning: kernels of one tile size are named 8 there
+  if (ns) *ns = hop_specialised(ctx->Ls, use_dense(ctx, prec)) ? ctx->tune[prec].ns : 8;
   if (order) *order = ctx->tune[prec].order;
   if (nf) *nf = ctx->tune[prec].nf;
   if (dense) *dense = use_dense(ctx, prec) ? 1 : 0;

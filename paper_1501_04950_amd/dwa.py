@@ -341,7 +341,8 @@ class Context:
 
         cache: path of a JSON file keyed by (GPU architecture, lattice, L_s, precision,
         batch reservation); a hit applies the stored configuration without timing, a
-        miss tunes and stores the result.  Returns {"ns", "order", "nf", "dense", "us",
+        miss (or a stored configuration that the library does not take) tunes and stores
+        the result.  Returns {"ns", "order", "nf", "dense", "us",
         "candidates", "cached"}; us is the chosen configuration's single-field hop-pair
         time (None when cached)."""
         p = PREC[prec] if isinstance(prec, str) else int(prec)
@@ -354,8 +355,13 @@ class Context:
             data = _load_tune_cache(cache)
             if key in data:
                 c = data[key]
-                self.set_tuning(p, c["ns"], c["order"], c["nf"], c["dense"])
-                return {**c, "us": None, "candidates": [], "cached": True}
+                try:
+                    self.set_tuning(p, c["ns"], c["order"], c["nf"], c["dense"])
+                    return {**c, "us": None, "candidates": [], "cached": True}
+                except DwaError as e:
+                    if e.status != DWA_EINVAL:
+                        raise
+                    # a configuration that this library does not take: tuned again below
         ent = (dwa_tune_entry * 48)()
         n = c_int(0)
         check(lib().dwa_autotune(self._h, p, int(reps), ent, 48, byref(n)))
