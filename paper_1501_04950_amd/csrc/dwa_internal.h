@@ -228,6 +228,8 @@ struct WaveHopArgs {
   FieldStrides in_st, post_st, out_st;
   unsigned Vh, Ls, parity, nrhs;
   unsigned spw;  // sites of a block per wave
+  unsigned spg;  // of them in one term of a norm; nsum norms per field
+  unsigned nsum;
 };
 // The matrix pairs of the four hops of D_bb and D_bb^dag, [WT_COUNT][unit, gamma part][2][64][4]
 // (chirality, lane, step) in the matrix-core operand order, zero beyond L_s.

@@ -149,6 +149,7 @@ template <typename R>
 constexpr int kWavePitch = sizeof(R) == 8 ? 18 : 20;
 template <typename R>
 constexpr int kWaveBuf = 24 * kWavePitch<R>;
+constexpr unsigned kWaveMaxSpw = 16;  // sites of a block per wave
 
 // FP64 / FP32 hop of one site: lane (s, spin g) = (lane / 4, lane % 4) multiplies the links
 // (wave-uniform, in scalar registers) onto its own spin of each neighbour and adds them to D
@@ -397,7 +398,7 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
   using M = WaveMix<S>;
   __shared__ __align__(16) R xbuf[BF ? 1 : NW][SPLIT ? 2 : 1][BF ? 4 : kWaveBuf<R>];
   __shared__ __align__(16) uint32_t ltab[NW][BF ? 72 * kLinkStep / 4 : 4];
-  __shared__ double wsum[NW];
+  __shared__ double wsum[NW * kWaveMaxSpw];
   extern __shared__ __align__(16) char tile_raw[];
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kq = lane >> 4;
@@ -432,6 +433,14 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
   };
   constexpr bool NORM = POST && OUTL != 2;  // (the tiled store serves operators without norms)
   double nrm = 0.0;
+  // Norms are summed over spg sites of a wave and then over four such terms, in an order that
+  // the sites of a wave do not change.  Term i of the block is complete:
+  const unsigned terms = a.spw / a.spg;  // of a wave
+  auto put_norm = [&](unsigned i) {
+    const double t = wave_sum(nrm);
+    if (lane == 0) wsum[i] = t;
+    nrm = 0.0;
+  };
 
   // x term of one site: the spins of chirality ch of the lane's slice and colour
   auto load_post = [&](__amdgpu_buffer_rsrc_t rp, unsigned cb, int ch, cpx<R> pv[2]) {
@@ -492,6 +501,7 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
     // and the other waves hide them).
     const unsigned first = site0 + wid * a.spw;
     const unsigned cnt = first >= site1 ? 0u : (site1 - first < a.spw ? site1 - first : a.spw);
+    unsigned in_term = 0, term = wid * terms;
     if (cnt) {
       const WaveSite row = wave_site(a.geo, first, a.parity);
       const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
@@ -512,13 +522,24 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
         mix(0, B0[0], B1[0], pv[0], o);
         mix(1, B0[1], B1[1], pv[1], o + 2);
         store(ro, w.cb, wid * a.spw + k, 0, std::integral_constant<int, 4>(), o);
+        if constexpr (NORM) {
+          if (a.partials && ++in_term == a.spg) {
+            put_norm(term++);
+            in_term = 0;
+          }
+        }
       }
+    }
+    if constexpr (NORM) {
+      if (a.partials)
+        for (; term < (wid + 1) * terms; ++term) put_norm(term);
     }
   } else {
     const int s4 = lane >> 2, g = lane & 3;
     const unsigned in_lane = (unsigned(s4 < Ls ? s4 : Ls - 1) * a.in_st.s + unsigned(g) * a.in_st.spin) * EB;
     R* buf = xbuf[wid][0];
     const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
+    unsigned in_term = 0, term = wid;
     for (unsigned k = 0; k < a.spw; ++k) {
       const unsigned idx = site0 + k * NW + wid;
       if (idx >= site1) break;
@@ -545,6 +566,17 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
         mix(ch, B0, B1, pv[ch], o);
         store(ro, w.cb, idx - site0, 2 * ch, std::integral_constant<int, 2>(), o);
       }
+      if constexpr (NORM) {
+        if (a.partials && ++in_term == a.spg) {
+          put_norm(term);
+          term += NW;
+          in_term = 0;
+        }
+      }
+    }
+    if constexpr (NORM) {
+      if (a.partials)
+        for (; term < NW * terms; term += NW) put_norm(term);
     }
   }
   if constexpr (OUTL == 2) {
@@ -559,15 +591,14 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
       if (site0 + j < site1) out[size_t(row) * a.Vh + w0.cb + j] = tile[row * (NSB + 1) + j];
     }
   }
-  if constexpr (POST) {
+  if constexpr (NORM) {
     if (a.partials) {
-      nrm = wave_sum(nrm);
-      if (lane == 0) wsum[wid] = nrm;
       __syncthreads();
-      if (threadIdx.x == 0) {
+      const unsigned i = site0 / (NW * a.spg) + threadIdx.x;
+      if (threadIdx.x < terms && i < a.nsum) {
         double t = 0.0;
-        for (int i = 0; i < NW; ++i) t += wsum[i];
-        a.partials[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = t;
+        for (int k = 0; k < NW; ++k) t += wsum[threadIdx.x * NW + k];
+        a.partials[size_t(blockIdx.y) * a.nsum + i] = t;
       }
     }
   }
@@ -883,20 +914,29 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
   // while enough waves are left to fill the 256 CUs; the tiled store wants 128-byte rows (32
   // sites of a block).  FP64 / FP32: one until the chip is full, then up to 16, which repay the
   // load of the matrices.
-  if (S::prec == DWA_BF16) {
-    const unsigned cap = tile || size_t(a.Vh) * ny >= 32768 ? 8 : (size_t(a.Vh) * ny >= 8192 ? 4 : 1);
-    a.spw = 1;
-    while (2 * a.spw <= cap && a.geo.Lxh % (2 * a.spw) == 0) a.spw *= 2;
-  } else if (tile) {
-    a.spw = NSB / NW;
-  } else {
-    a.spw = 1;
-    while (a.spw < 16 && size_t(a.Vh) * ny / (2 * NW * a.spw) >= 4096) a.spw *= 2;
-  }
+  auto sites_per_wave = [&](size_t sites) {
+    unsigned spw = 1;
+    if (S::prec == DWA_BF16) {
+      const unsigned cap = tile || sites >= 32768 ? 8 : (sites >= 8192 ? 4 : 1);
+      while (2 * spw <= cap && a.geo.Lxh % (2 * spw) == 0) spw *= 2;
+    } else if (tile) {
+      spw = NSB / NW;
+    } else {
+      while (spw < kWaveMaxSpw && sites / (2 * NW * spw) >= 4096) spw *= 2;
+    }
+    return spw;
+  };
+  a.spw = sites_per_wave(size_t(a.Vh) * ny);
+  // Norms are grouped by the lattice alone, so that a batch's field sums them as its own solve
+  // does (both are powers of two).  The further sums of a wave cost a batch 0 to 4% of an
+  // iteration (BF16, 12 fields of 8^3 x 16, L_s = 12: 244 -> 251 us; FP64, L_s = 9: 613 ->
+  // 628), where giving every wave the sites of the single solve costs up to 10 (257, 633).
+  a.spg = sites_per_wave(a.Vh);
+  a.nsum = (a.Vh + NW * a.spg - 1) / (NW * a.spg);
   const unsigned nblk = (a.Vh + NW * a.spw - 1) / (NW * a.spw);
   const dim3 grid(nblk, ny);
   const size_t shm = tile ? size_t(12) * a.Ls * (NSB + 1) * EB : 0;
-  if (nparts) *nparts = int(nblk);
+  if (nparts) *nparts = int(a.nsum);
 #define DWA_WAVE(SPLIT, POST, INSM, OUTL) \
   hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL>), grid, dim3(256), shm, ctx->stream, a)
   if (split) {

@@ -1,0 +1,38 @@
+"""A field of a batched CGLS against its own solve, bit for bit."""
+
+import pytest
+
+from paper_1501_04950_amd import dwa, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# lattices of the wave hop and of the site blocks; batches on both sides of the sites from
+# which a hop without norms gives a wave several sites (32768; BF16 8192)
+CASES = [((4, 4, 4, 4), 8, 12, "f64"), ((8, 8, 8, 16), 9, 9, "f64"), ((8, 4, 4, 8), 12, 3, "f64"),
+         ((8, 8, 8, 8), 12, 3, "f64"), ((8, 8, 8, 16), 9, 9, "f32"), ((8, 8, 8, 16), 12, 6, "bf16")]
+
+
+
+@pytest.mark.parametrize("dims,Ls,n,inner", CASES)
+def test_batch_follows_its_single_solves(dims, Ls, n, inner):
+    """The same iterations of every source in one batch and alone, with one fold of a mixed
+    solve at the end.  (Sources of whole numbers: their norms, by which a mixed solve scales
+    them and which a batch sums on the host, are exact.)"""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[gpu] batch bits {dims} Ls={Ls} {inner} x{n}", flush=True)
+    ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
+    ctx.set_links(torch.from_numpy(synth.su3_field(dims, 0.5, 7)).cuda())
+    ctx.reserve_batch(n)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rhs = torch.stack([ctx.half_field("f64") for _ in range(n)]).contiguous()
+    re, im = (torch.randint(-1, 2, rhs.shape, generator=gen, device="cuda").double() for _ in range(2))
+    rhs.copy_(torch.complex(re, im))
+    o = dict(tol=1e-12, inner_prec=inner, delta=1e-3, maxiter=24, check_every=4)
+    xs, st, _ = dwa.cgne_solve_batch([(ctx, rhs)], **o)
+    for k in range(n):
+        x, s, _ = ctx.cgne_solve(rhs[k].contiguous(), **o)
+        assert st[0][k]["iters"] == s["iters"] and st[0][k]["outer"] == s["outer"]
+        assert torch.equal(xs[0][k], x), (k, float((xs[0][k] - x).abs().max() / x.abs().max()))
+    ctx.close()
