@@ -289,11 +289,11 @@ int launch_cg_update1(dwa_ctx* ctx, int prec, void* x, void* r, void* w, const v
                       int nrhs, const double* qparts, int nq, const double* zparts, int nz) {
   if (nrhs > 1 && serial("up1")) {
     const size_t n = field_elems(ctx);
+    int nb = 0;  // of one field: the same for every field
     for (int f = 0; f < nrhs; ++f) {
-      int nb = 0;
       int rc = launch_cg_update1(ctx, prec, fshift(x, xacc_prec(prec), n, f), fshift(r, prec, n, f),
                                  fshift(w, prec, n, f), fshift(p, prec, n, f), fshift(q, prec, n, f), s + f,
-                                 partials + size_t(f) * ((6 * ctx->Vh + 255) / 256), &nb, adj, 1,
+                                 partials + size_t(f) * nb, &nb, adj, 1,
                                  qparts ? qparts + size_t(f) * nq : nullptr, nq,
                                  zparts ? zparts + size_t(f) * nz : nullptr, nz);
       if (rc) return rc;

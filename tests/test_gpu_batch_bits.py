@@ -36,3 +36,27 @@ def test_batch_follows_its_single_solves(dims, Ls, n, inner):
         assert st[0][k]["iters"] == s["iters"] and st[0][k]["outer"] == s["outer"]
         assert torch.equal(xs[0][k], x), (k, float((xs[0][k] - x).abs().max() / x.abs().max()))
     ctx.close()
+
+
+@pytest.mark.parametrize("what", ["up1", "up2", "hopall", "smix"])
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+def test_serial_launches_give_the_batch(inner, what, monkeypatch):
+    """DWA_BATCH_SERIAL runs the named batched kernels field by field: the same solve."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[gpu] serial {what} {inner}", flush=True)
+    dims, Ls, n = (8, 8, 8, 8), 8, 3  # (site-block kernels)
+    ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
+    ctx.set_links(torch.from_numpy(synth.su3_field(dims, 0.3, 7)).cuda())
+    ctx.reserve_batch(n)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rhs = torch.stack([ctx.half_field("f64") for _ in range(n)]).contiguous()
+    rhs.copy_(torch.randn(rhs.shape, dtype=rhs.dtype, device="cuda", generator=gen))
+    o = dict(tol=1e-6, inner_prec=inner, delta=0.1, maxiter=600, check_every=3)
+    xs, st, rc = dwa.cgne_solve_batch([(ctx, rhs)], **o)
+    monkeypatch.setenv("DWA_BATCH_SERIAL", what)
+    ys, tt, rd = dwa.cgne_solve_batch([(ctx, rhs)], **o)
+    assert rc == rd == dwa.DWA_OK
+    assert [s["iters"] for s in st[0]] == [t["iters"] for t in tt[0]]
+    assert torch.equal(xs[0], ys[0])
+    ctx.close()
