@@ -192,6 +192,9 @@ bool serial(const char* what) {
   const char* e = std::getenv("DWA_BATCH_SERIAL");
   return e && std::strstr(e, what) != nullptr;
 }
+bool serial_hop(const double* partials) {
+  return serial("hop,") || serial("hopall") || (partials && serial("hopp")) || (!partials && serial("hopn"));
+}
 template <typename T>
 T* fshift(T* p, int prec, size_t n, int f) {
   return p ? reinterpret_cast<T*>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char>*>(p) +
@@ -201,8 +204,7 @@ T* fshift(T* p, int prec, size_t n, int f) {
 }  // namespace
 
 int launch_hop(dwa_ctx* ctx, int prec, const HopOp& op, int* nblocks_out) {
-  if (op.nrhs > 1 && (serial("hop,") || serial("hopall") || (op.partials && serial("hopp")) ||
-                      (!op.partials && serial("hopn")))) {
+  if (op.nrhs > 1 && serial_hop(op.partials)) {
     const size_t n = field_elems(ctx);
     for (int f = 0; f < op.nrhs; ++f) {
       HopOp o = op;
@@ -233,6 +235,22 @@ int launch_hop(dwa_ctx* ctx, int prec, const HopOp& op, int* nblocks_out) {
   DWA_DISPATCH(prec, launch_hop_p<S_>(ctx, op, nblocks_out));
 }
 int launch_wave_hop(dwa_ctx* ctx, int prec, const WaveOp& op, int* nparts) {
+  if (op.nrhs > 1 && serial_hop(op.partials)) {
+    const size_t n = field_elems(ctx);
+    int nb = 0;  // of one field: the same for every field
+    for (int f = 0; f < op.nrhs; ++f) {
+      WaveOp o = op;
+      o.nrhs = 1;
+      o.in = fshift(op.in, prec, n, f);
+      o.out = fshift(op.out, prec, n, f);
+      o.post = fshift(op.post, prec, n, f);
+      if (op.partials) o.partials = op.partials + size_t(f) * nb;
+      const int rc = launch_wave_hop(ctx, prec, o, &nb);
+      if (rc) return rc;
+    }
+    if (nparts) *nparts = nb;
+    return DWA_OK;
+  }
   DWA_DISPATCH(prec, launch_wave_hop_p<S_>(ctx, op, nparts));
 }
 int launch_to_sm(dwa_ctx* ctx, int prec, void* dst, int prec_in, const void* src, double scale, int nrhs,
@@ -258,10 +276,31 @@ int launch_fold_sm(dwa_ctx* ctx, void* X, void* xl, double scale, int nrhs, cons
 int launch_vec_update1(dwa_ctx* ctx, int prec, void* x, void* r, const void* p, const void* q, DevScalars* s,
                        double* partials, int* nblocks, int nrhs, const double* qparts, int nq, const double* zparts,
                        int nz) {
+  if (nrhs > 1 && serial("up1")) {
+    const size_t n = field_elems(ctx);
+    int nb = 0;  // of one field: the same for every field
+    for (int f = 0; f < nrhs; ++f) {
+      const int rc = launch_vec_update1(ctx, prec, fshift(x, xacc_prec(prec), n, f), fshift(r, prec, n, f),
+                                        fshift(p, prec, n, f), fshift(q, prec, n, f), s + f, partials + size_t(f) * nb,
+                                        &nb, 1, qparts + size_t(f) * nq, nq, zparts + size_t(f) * nz, nz);
+      if (rc) return rc;
+    }
+    if (nblocks) *nblocks = nb;
+    return DWA_OK;
+  }
   DWA_DISPATCH(prec, launch_vec_update1_p<S_>(ctx, x, r, p, q, s, partials, nblocks, nrhs, qparts, nq, zparts, nz));
 }
 int launch_vec_update2(dwa_ctx* ctx, int prec, void* p, const void* z, DevScalars* s, int nrhs, const double* zparts,
                        int nz) {
+  if (nrhs > 1 && serial("up2")) {
+    const size_t n = field_elems(ctx);
+    for (int f = 0; f < nrhs; ++f) {
+      const int rc = launch_vec_update2(ctx, prec, fshift(p, prec, n, f), fshift(z, prec, n, f), s + f, 1,
+                                        zparts + size_t(f) * nz, nz);
+      if (rc) return rc;
+    }
+    return DWA_OK;
+  }
   DWA_DISPATCH(prec, launch_vec_update2_p<S_>(ctx, p, z, s, nrhs, zparts, nz));
 }
 int launch_gather_links(dwa_ctx* ctx, int prec, void* dst, const void* src) {

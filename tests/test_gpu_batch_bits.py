@@ -39,13 +39,14 @@ def test_batch_follows_its_single_solves(dims, Ls, n, inner):
 
 
 @pytest.mark.parametrize("what", ["up1", "up2", "hopall", "smix"])
+@pytest.mark.parametrize("Ls", [8, 9])  # site-block kernels, wave hop
 @pytest.mark.parametrize("inner", ["f64", "f32"])
-def test_serial_launches_give_the_batch(inner, what, monkeypatch):
+def test_serial_launches_give_the_batch(inner, Ls, what, monkeypatch):
     """DWA_BATCH_SERIAL runs the named batched kernels field by field: the same solve."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    print(f"[gpu] serial {what} {inner}", flush=True)
-    dims, Ls, n = (8, 8, 8, 8), 8, 3  # (site-block kernels)
+    print(f"[gpu] serial {what} {inner} Ls={Ls}", flush=True)
+    dims, n = (8, 8, 8, 8), 3
     ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
     ctx.set_links(torch.from_numpy(synth.su3_field(dims, 0.3, 7)).cuda())
     ctx.reserve_batch(n)
