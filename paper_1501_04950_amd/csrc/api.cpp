@@ -1495,7 +1495,8 @@ int dwa_create(dwa_ctx** out, const dwa_params* p, void* stream) {
     ctx->wgeo = WaveGeo{unsigned(Lx / 2), unsigned(Ly), unsigned(Lz), unsigned(Lt), unsigned(Lz),
                         magic(Lx / 2), magic(Ly), magic(Lz), magic(Lt)};
     ctx->wgeo_mzdom = Lz % 8 == 0 ? magic(Lz / 8) : 0u;
-    ctx->wave_geo_ok = Vh * std::max(std::max(Lx, Ly), std::max(Lz, Lt)) < (1LL << 32);
+    ctx->wave_geo_ok = Vh * std::max(std::max(Lx, Ly), std::max(Lz, Lt)) < (1LL << 32) &&
+                       !std::getenv("DWA_NO_WAVE_HOP");
   }
   // s-matrices
   if ((rc = upload_smatrices(ctx, mix, sweeps, true))) return fail(rc);

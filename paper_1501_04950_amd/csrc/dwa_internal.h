@@ -330,7 +330,7 @@ struct dwa_ctx {
   float* d_wave32 = nullptr;
   dwa::WaveGeo wgeo = {};          // wave hop walk; wgeo_mzdom: reciprocal of Lz / 8
   unsigned wgeo_mzdom = 0;
-  bool wave_geo_ok = false;        // the walk's reciprocals are exact on this lattice
+  bool wave_geo_ok = false;        // the walk's reciprocals are exact on this lattice (and not DWA_NO_WAVE_HOP)
   std::vector<int> sweep_meta_host;
   bool dense_mix = false;          // some sweep program failed its check: dense matrices
   size_t hop_min_lds = 0;          // lower bound on a fused hop block's LDS (limits occupancy)

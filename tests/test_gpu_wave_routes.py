@@ -1,0 +1,114 @@
+"""The wave hop's own forms: its tiled batches, several sites per wave and its walk, and the
+site-major solvers of L_s = 6, 10 and 14."""
+
+import numpy as np
+import pytest
+
+from oracle import redblack
+from paper_1501_04950_amd import dwa, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-13, "f32": 2e-6, "bf16": 2e-2}  # as in the parity tests
+
+
+def context(dims, Ls, U, batch=0):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
+    ctx.set_links(torch.from_numpy(U).cuda())
+    if batch:
+        ctx.reserve_batch(batch)
+    return ctx
+
+
+# BF16 batches above 2 MB, which pass through the tiled store: L_s of the site blocks too
+# (6144 sites at most for L_s = 8), rows of 1 to 11 sites, z of one plane group and of eight;
+# 16 and 22 sites of x: eight of a wave in a row, and across rows
+TILED = [((2, 2, 6, 2), 8, 240), ((10, 2, 2, 6), 8, 48), ((6, 2, 4, 2), 12, 80), ((14, 2, 2, 2), 12, 140),
+         ((16, 2, 2, 4), 12, 40), ((16, 2, 16, 2), 16, 6), ((6, 2, 16, 2), 16, 16), ((22, 2, 2, 2), 16, 70),
+         ((12, 6, 16, 2), 9, 7)]
+
+
+@pytest.mark.parametrize("dims,Ls,n", TILED)
+def test_tiled_batches(dims, Ls, n):
+    """D_bb of such a batch and its norms against D_bb of one field read in place, which the
+    oracle checks."""
+    U = synth.su3_field(dims, 0.5, 3)
+    rb = redblack.RedBlack(U, redblack.Params.make(dims, Ls, -1.8, 0.05, 0.8, np.full(Ls, 1.5), np.full(Ls, 0.5)))
+    f = synth.gaussian_field5(dims, Ls, 11) * rb.black
+    ctx = context(dims, Ls, U, n)
+    print(f"[gpu] tiled wave batch {dims} Ls={Ls} x{n}", flush=True)
+    x = ctx.pack(torch.from_numpy(f).cuda(), 0, "bf16")
+    assert n * x.numel() * x.element_size() > 2 << 20
+    xs = torch.stack([x * (1 + k % 3) for k in range(n)]).contiguous()
+    ys, nrm = ctx.apply_Dbb_batch(xs, "bf16", norms=True)
+    for k in range(3):
+        y = ctx.apply_Dbb(xs[k].contiguous(), "bf16")
+        for j in range(k, n, 3):
+            assert torch.equal(ys[j], y), j
+            want = float(y.double().square().sum())
+            assert abs(nrm[j] - want) <= 1e-5 * want
+    out = torch.zeros(f.shape, dtype=torch.complex128, device="cuda")
+    ctx.unpack(ys[0], 0, "bf16", out=out)
+    ref = rb.Dbb(f)
+    assert np.linalg.norm(out.cpu().numpy() - ref) < TOL["bf16"] * np.linalg.norm(ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("dims,Ls,n", [((4, 2, 16, 2), 9, 3), ((6, 2, 16, 4), 7, 3), ((2, 4, 32, 2), 13, 2),
+                                       ((16, 2, 2, 4), 3, 260), ((6, 2, 16, 4), 3, 180)])
+def test_walk_and_sites_per_wave(dims, Ls, n, prec):
+    """z-plane groups, and batches of 32768 sites and more, whose waves take several sites
+    each: D_bb and D_bb^dag against the oracle, the batch bit for bit the single call."""
+    U = synth.su3_field(dims, 0.5, 3)
+    rb = redblack.RedBlack(U, redblack.Params.make(dims, Ls, -1.8, 0.05, 0.8, np.full(Ls, 1.5), np.full(Ls, 0.5)))
+    f = synth.gaussian_field5(dims, Ls, 11) * rb.black
+    ctx = context(dims, Ls, U, n)
+    print(f"[gpu] wave walk {dims} Ls={Ls} {prec} x{n}", flush=True)
+    x = ctx.pack(torch.from_numpy(f).cuda(), 0, prec)
+    first = None
+    for order in ("slab", "lex", "zdom"):
+        ctx.set_tuning(prec, 8, order)
+        got = ctx.apply_Dbb(x, prec), ctx.apply_Dbb_dag(x, prec)
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first)), order
+    xs = torch.stack([x * (1 + k % 3) for k in range(n)]).contiguous()
+    ys = ctx.apply_Dbb_batch(xs, prec)
+    for k in range(min(n, 3)):
+        y = ctx.apply_Dbb(xs[k].contiguous(), prec)
+        assert all(torch.equal(ys[j], y) for j in range(k, n, 3))
+    for half, ref in zip(first, (rb.Dbb(f), rb.Dbb_dag(f))):
+        out = torch.zeros(f.shape, dtype=torch.complex128, device="cuda")
+        ctx.unpack(half, 0, prec, out=out)
+        assert np.linalg.norm(out.cpu().numpy() - ref) < TOL[prec] * np.linalg.norm(ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("inner,delta", [("f64", 0.1), ("f32", 0.02), ("bf16", 0.3)])
+@pytest.mark.parametrize("Ls", [6, 10, 14])
+def test_even_ls_solvers(Ls, inner, delta):
+    """Site-major solvers of one source and of a batch against those of the dense kernels: both
+    residuals are below tol, so the propagators agree to kappa * tol."""
+    dims, tol, n = (4, 2, 4, 6), 1e-11, 3
+    U = synth.su3_field(dims, 0.3, 5)
+    ctx = context(dims, Ls, U, n)
+    print(f"[gpu] wave solve Ls={Ls} {inner}", flush=True)
+    V = int(np.prod(dims))
+    eta = np.stack([synth.point_source(dims, 1, k // 3, k % 3) for k in range(n)]).reshape(n, V, 4, 3)
+    eta = torch.from_numpy(eta).cuda()
+    o = dict(tol=tol, inner_prec=inner, delta=delta, check_every=3)
+    ys, st, rc = ctx.propagator_batch(eta, **o)
+    assert rc == dwa.DWA_OK
+    for k in range(n):
+        y, s, rc = ctx.propagator(eta[k].contiguous(), **o)
+        ctx.set_tuning(inner, 8, "slab", 1, True)
+        g, sg, rcg = ctx.propagator(eta[k].contiguous(), **o)
+        ctx.set_tuning(inner, 8, "slab", 1, False)
+        assert rc == rcg == dwa.DWA_OK
+        assert max(s["rel_resid"], sg["rel_resid"], st[k]["rel_resid"]) <= 1.01 * tol
+        for a in (y, ys[k]):
+            assert float(torch.linalg.vector_norm(a - g)) <= 1e-8 * float(torch.linalg.vector_norm(g))
+    ctx.close()
