@@ -192,8 +192,8 @@ int dwa_apply_hop(dwa_ctx *ctx, int prec, int parity_out, int kind, void *out, c
  * order, 2 = z-planes per XCD.  Only the assignment of sites to blocks changes: every
  * site's arithmetic is the same, so D_bb and every hop output are bitwise identical
  * across configurations (CG reductions group their partial sums by block, so solver
- * scalars can differ in the last bits).  The hop with one wavefront per site has no tile: it
- * takes the order and nf alone.  The defaults are ns = 16 for FP64, 32 for
+ * scalars can differ in the last bits).  The hop with one wavefront per site takes none of
+ * them: no tile, an order of its own, one field per block.  The defaults are ns = 16 for FP64, 32 for
  * FP32 / BF16, order 0. */
 typedef struct {
   int prec;  /* storage precision */
@@ -205,7 +205,10 @@ typedef struct {
   int nrhs;  /* fields the configuration was timed on (1, or a batch) */
   double us; /* average time of one hop pair of D_bb (N hop, then G^-1 I^-1 hop with the
                 x term) on nrhs fields, microseconds; negative if the configuration
-                cannot run here (its LDS exceeds the device limit) */
+                cannot run here (its LDS exceeds the device limit).  Where D_bb of one
+                field runs the hop with one wavefront per site, every entry with dense = 0
+                and nrhs = 1 holds the time of that hop's pair, on fields in its layout;
+                entries of a batch are always the site-block hop's. */
 } dwa_tune_entry;
 
 /* Autotuner: time every tile and order of precision prec on this context's lattice,

@@ -1814,9 +1814,9 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
     void* q = W[p64 ? W_Q : L_Q];
     if ((rc = launch_zero(ctx, prec, x, n)) == DWA_OK) rc = launch_zero(ctx, prec, t, n);
     for (size_t k = 0; k < cands.size() && rc == DWA_OK; ++k) rc = time_pair(cands[k], x, t, q, false);
-    // Where D_bb of one field takes the wave hop, every tile of the sweeps stands for its
-    // time (against the dense matrices), and among themselves the tiles are ranked by the
-    // site-block kernels, which larger calls of the context run.
+    // Where D_bb of one field takes the wave hop, which has neither tile nor order, every one
+    // of the sweeps stands for its time (against the dense matrices), and among themselves
+    // they are ranked by the site-block kernels, which larger calls of the context run.
     ctx->tune[prec] = cands[0].t;
     if (rc == DWA_OK && use_wave_soa(ctx, prec, 1)) {
       Cand w{cands[0].t, 1, -1.0};
@@ -1848,10 +1848,8 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
       c.nf = nf;
       cands.push_back(Cand{c, nb, -1.0});
     }
-    for (size_t k = from; k < cands.size() && rc == DWA_OK; ++k) {
-      ctx->tune[prec] = cands[k].t;
-      rc = time_pair(cands[k], x, t, q, use_wave_soa(ctx, prec, nb));
-    }
+    // (by the site-block hop also where this batch would not run it: larger ones do)
+    for (size_t k = from; k < cands.size() && rc == DWA_OK; ++k) rc = time_pair(cands[k], x, t, q, false);
     const long long bb = rc == DWA_OK ? best_of(from) : -1;
     if (bb >= 0) chosen.nf = cands[size_t(bb)].t.nf;
   }

@@ -59,3 +59,35 @@ def test_refused_cache_entry_is_tuned_again(tmp_path):
     assert json.load(open(cache))[key]["ns"] == 8
     assert ctx.autotune("f64", reps=2, cache=cache)["cached"]
     ctx.close()
+
+
+def test_fields_per_block_are_timed_by_the_hop_that_has_them(monkeypatch):
+    """The autotuner's times of the fields per block are the site-block hop's, also where this
+    batch runs the wave hop (which takes about 0.4 of its time here)."""
+    dims, Ls = (8, 8, 8, 8), 9
+    ctx = context(dims, Ls, 12)
+    monkeypatch.setenv("DWA_NO_WAVE_HOP", "1")
+    ref = context(dims, Ls, 12)
+    us = []
+    for c in (ctx, ref):
+        t = c.autotune("bf16", reps=10)["candidates"]
+        us.append(min(e["us"] for e in t if e["nrhs"] > 1 and e["us"] >= 0))
+    print(f"[gpu] fields per block: {us[0]:.1f} us, without the wave hop {us[1]:.1f}", flush=True)
+    assert us[0] > 0.7 * us[1]
+    ctx.close()
+    ref.close()
+
+
+def test_wave_solve_does_not_depend_on_the_order():
+    """The wave hop's walk follows from the lattice, so its sums do not move with a tuning."""
+    dims, Ls = (4, 2, 16, 8), 9
+    ctx = context(dims, Ls)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rhs = ctx.half_field("f64")
+    rhs.copy_(torch.randn(rhs.shape, dtype=rhs.dtype, device="cuda", generator=gen))
+    xs = []
+    for order in ("slab", "lex", "zdom"):
+        ctx.set_tuning("f64", 8, order)
+        xs.append(ctx.cgne_solve(rhs, tol=1e-12, maxiter=40, check_every=8)[0].clone())
+    assert torch.equal(xs[0], xs[1]) and torch.equal(xs[0], xs[2])
+    ctx.close()
