@@ -110,9 +110,9 @@ int wave_dbb(dwa_ctx* ctx, int prec, bool dag, void* out, const void* in, void* 
 
 // The same on SoA fields.  Up to 2 MB, which stays in the caches, are read and written in
 // place, by 4 to 16 bytes a lane; more passes through a site-major copy of the input (tb) and
-// a tiled store, so that every access is whole lines (BF16, L_s = 8, 12 fields of 4096 sites:
-// 155 us in place, 69 us so).  The tiled store sums no
-// norms, so with partials the output is read once more.
+// a tiled store, whose rows are whole lines (BF16: of 12 to 32 sites, see sites_per_wave;
+// L_s = 8, 12 fields of 4096 sites: 155 us in place, 69 us so).  The tiled store sums no norms,
+// so with partials the output is read once more.
 constexpr size_t kWaveDirectBytes = size_t(2) << 20;
 int wave_dbb_soa(dwa_ctx* ctx, int prec, bool dag, void* out, const void* in, void* tb, void* tr, int nrhs = 1,
                  double* partials = nullptr, int* nparts = nullptr) {

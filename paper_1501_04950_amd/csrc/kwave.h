@@ -388,7 +388,8 @@ __device__ __forceinline__ void wave_hop_bf16(const uint32_t* tab, const WaveLin
 // than one wave per site was no faster on 4^4 (44 against 42 us) and slower from 8^4 on.
 //   INSM   the input is site-major (BF16 reads four spins at once); else by strides
 //   OUTL   0: by strides; 1: site-major; 2: SoA through an LDS tile of the block's sites
-template <typename S, bool SPLIT, bool POST, bool INSM, int OUTL>
+//   CROSS  (BF16) a wave's sites go on across the ends of x rows
+template <typename S, bool SPLIT, bool POST, bool INSM, int OUTL, bool CROSS>
 __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_kernel(WaveHopArgs a) {
   using R = RealOf<S>;
   using E = typename S::elem;
@@ -496,88 +497,94 @@ __global__ void __launch_bounds__(256, S::prec == DWA_BF16 ? 5 : 1) wave_hop_ker
     unsigned lane_c[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) lane_c[j] = (sc * a.in_st.s + unsigned((j + kq) % 3) * a.in_st.col) * EB;
-    // The wave's sites are consecutive in x (the launcher sees to it).  The next site's links
-    // are loaded ahead; the neighbours are not (their registers would cost a wave per SIMD,
-    // and the other waves hide them).
+    // The wave's sites are consecutive in the walk; without CROSS they are in one x row (the
+    // launcher sees to it).  The next site's links are loaded ahead within a row; the
+    // neighbours are not (their registers would cost a wave per SIMD, and the other waves hide
+    // them).
     const unsigned first = site0 + wid * a.spw;
     const unsigned cnt = first >= site1 ? 0u : (site1 - first < a.spw ? site1 - first : a.spw);
-    unsigned in_term = 0, term = wid * terms;
+    unsigned term = wid * terms;
     if (cnt) {
-      const WaveSite row = wave_site(a.geo, first, a.parity);
+      WaveSite row = wave_site(a.geo, first, a.parity);
       const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
       uint2 lk = wave_load_links(a, row.cb, lane);
-      for (unsigned k = 0; k < cnt; ++k) {
-        WaveSite w;
-        wave_row_step(a.geo, row, k, w);
-        WaveIn v;
-        wave_load_bf16<INSM>(a, ri, w, lane_c, kq, v);
-        cpx<R> pv[2][2];
-        load_post(rp, w.cb, 0, pv[0]);
-        load_post(rp, w.cb, 1, pv[1]);
-        wave_stage_links(ltab[wid], lane, lk);
-        if (k + 1 < cnt) lk = wave_load_links(a, w.cb + 1, lane);
-        dwa_f4 B0[2], B1[2];
-        wave_hop_bf16<SPLIT>(ltab[wid], ll, v, B0, B1);
-        cpx<R> o[4];
-        mix(0, B0[0], B1[0], pv[0], o);
-        mix(1, B0[1], B1[1], pv[1], o + 2);
-        store(ro, w.cb, wid * a.spw + k, 0, std::integral_constant<int, 4>(), o);
-        if constexpr (NORM) {
-          if (a.partials && ++in_term == a.spg) {
-            put_norm(term++);
-            in_term = 0;
+      unsigned k = 0, k0 = 0;  // k0: where the row began
+      do {
+        const unsigned end = NORM && k + a.spg < cnt ? k + a.spg : cnt;
+        for (; k < end; ++k) {
+          if constexpr (CROSS) {
+            if (row.xh + (k - k0) == a.geo.Lxh) {
+              row = wave_site(a.geo, first + k, a.parity);
+              k0 = k;
+              lk = wave_load_links(a, row.cb, lane);
+            }
           }
+          WaveSite w;
+          wave_row_step(a.geo, row, k - k0, w);
+          WaveIn v;
+          wave_load_bf16<INSM>(a, ri, w, lane_c, kq, v);
+          cpx<R> pv[2][2];
+          load_post(rp, w.cb, 0, pv[0]);
+          load_post(rp, w.cb, 1, pv[1]);
+          wave_stage_links(ltab[wid], lane, lk);
+          if (k + 1 < cnt && (!CROSS || w.xh + 1 < a.geo.Lxh)) lk = wave_load_links(a, w.cb + 1, lane);
+          dwa_f4 B0[2], B1[2];
+          wave_hop_bf16<SPLIT>(ltab[wid], ll, v, B0, B1);
+          cpx<R> o[4];
+          mix(0, B0[0], B1[0], pv[0], o);
+          mix(1, B0[1], B1[1], pv[1], o + 2);
+          store(ro, w.cb, wid * a.spw + k, 0, std::integral_constant<int, 4>(), o);
         }
-      }
+        if constexpr (NORM) {
+          if (a.partials) put_norm(term++);
+        }
+      } while (k < cnt);
     }
-    if constexpr (NORM) {
-      if (a.partials)
-        for (; term < (wid + 1) * terms; ++term) put_norm(term);
+    if constexpr (NORM) {  // (terms beyond the lattice)
+      for (; term < (wid + 1) * terms; ++term)
+        if (lane == 0) wsum[term] = 0.0;
     }
   } else {
     const int s4 = lane >> 2, g = lane & 3;
     const unsigned in_lane = (unsigned(s4 < Ls ? s4 : Ls - 1) * a.in_st.s + unsigned(g) * a.in_st.spin) * EB;
     R* buf = xbuf[wid][0];
     const __amdgpu_buffer_rsrc_t ri = field(a.in), rp = field(POST ? a.post : a.in), ro = field(a.out);
-    unsigned in_term = 0, term = wid;
-    for (unsigned k = 0; k < a.spw; ++k) {
-      const unsigned idx = site0 + k * NW + wid;
-      if (idx >= site1) break;
-      const WaveSite w = wave_site(a.geo, idx, a.parity);
-      cpx<R> pv[2][2];
-      load_post(rp, w.cb, 0, pv[0]);
-      load_post(rp, w.cb, 1, pv[1]);
-      cpx<R> D[3], T[3];
-      wave_hop_valu<S>(a, ri, w, in_lane, g, D, T);
-      if constexpr (!SPLIT) {
+    unsigned term = wid, k = 0;
+    do {
+      const unsigned end = NORM ? k + a.spg : a.spw;
+      for (; k < end; ++k) {
+        const unsigned idx = site0 + k * NW + wid;
+        if (idx >= site1) break;
+        const WaveSite w = wave_site(a.geo, idx, a.parity);
+        cpx<R> pv[2][2];
+        load_post(rp, w.cb, 0, pv[0]);
+        load_post(rp, w.cb, 1, pv[1]);
+        cpx<R> D[3], T[3];
+        wave_hop_valu<S>(a, ri, w, in_lane, g, D, T);
+        if constexpr (!SPLIT) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) D[k] = D[k] + T[k];
-      }
-      wave_lds_sync();
-      wave_put<R>(buf, s4, g, D);
-      if constexpr (SPLIT) wave_put<R>(xbuf[wid][SPLIT ? 1 : 0], s4, g, T);
-      wave_lds_sync();
+          for (int c = 0; c < 3; ++c) D[c] = D[c] + T[c];
+        }
+        wave_lds_sync();
+        wave_put<R>(buf, s4, g, D);
+        if constexpr (SPLIT) wave_put<R>(xbuf[wid][SPLIT ? 1 : 0], s4, g, T);
+        wave_lds_sync();
 #pragma unroll
-      for (int ch = 0; ch < 2; ++ch) {
-        const acc4<M> B0 = wave_get<M>(buf, lane, ch);
-        acc4<M> B1 = B0;
-        if constexpr (SPLIT) B1 = wave_get<M>(buf + kWaveBuf<R>, lane, ch);
-        cpx<R> o[2];
-        mix(ch, B0, B1, pv[ch], o);
-        store(ro, w.cb, idx - site0, 2 * ch, std::integral_constant<int, 2>(), o);
-      }
-      if constexpr (NORM) {
-        if (a.partials && ++in_term == a.spg) {
-          put_norm(term);
-          term += NW;
-          in_term = 0;
+        for (int ch = 0; ch < 2; ++ch) {
+          const acc4<M> B0 = wave_get<M>(buf, lane, ch);
+          acc4<M> B1 = B0;
+          if constexpr (SPLIT) B1 = wave_get<M>(buf + kWaveBuf<R>, lane, ch);
+          cpx<R> o[2];
+          mix(ch, B0, B1, pv[ch], o);
+          store(ro, w.cb, idx - site0, 2 * ch, std::integral_constant<int, 2>(), o);
         }
       }
-    }
-    if constexpr (NORM) {
-      if (a.partials)
-        for (; term < NW * terms; term += NW) put_norm(term);
-    }
+      k = end;
+      if constexpr (NORM) {
+        if (a.partials) put_norm(term);
+        term += NW;
+      }
+    } while (k < a.spw);
   }
   if constexpr (OUTL == 2) {
     // the block's sites are consecutive checkerboard indices (the launcher sees to it)
@@ -895,30 +902,27 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
   a.out_st = op.out_soa ? soa_strides(ctx) : sm_strides(ctx);
   const bool split = op.table == WT_DBB1 || op.table == WT_DAG1;
   const bool tile = op.out_soa && !op.post_soa;
-  // The walk: each XCD's range a group of Lz / 8 z-planes, walked in t, where that is two
-  // planes or more (against plain order: 16^3 x 32, solves 0 to 2% and D_bb 0 to 5% less time;
-  // 6 x 16^3 and 16^4 the same within 1%); of a single plane the neighbours in z are all
-  // another XCD's (8^4 and 8^3 x 16: D_bb 0 to 12% more, solves 0 to 3).  The tiled store takes plain
-  // order unless a plane is whole blocks, whose sites must be consecutive.
   a.geo = ctx->wgeo;
-  if (ctx->dims[2] % 8 == 0 && ctx->dims[2] >= 16 && !(tile && (a.geo.Lxh * a.geo.Ly) % NSB != 0)) {
-    a.geo.ZB = (unsigned)ctx->dims[2] / 8;
-    a.geo.mZB = ctx->wgeo_mzdom;
-  }
   // one field per block: with the links of a site shared by several, a block's fields run one
   // after the other (BF16 iteration of 12 fields of 12^3 x 24, L_s = 12: 1194 us; two fields a
   // block 1554, twelve 1359)
   const unsigned ny = a.nrhs;
   constexpr unsigned NW = 4;  // waves of a block
-  // Sites per wave.  BF16: consecutive ones of an x row, whose links are loaded a site ahead,
-  // while enough waves are left to fill the 256 CUs; the tiled store wants 128-byte rows (32
-  // sites of a block).  FP64 / FP32: one until the chip is full, then up to 16, which repay the
-  // load of the matrices.
+  // Sites per wave.  BF16: consecutive ones, whose links are loaded a site ahead, while enough
+  // waves are left to fill the 256 CUs; the tiled store wants 128-byte rows (32 sites of a
+  // block).  Of an x row where three or more of its sites divide it, else across row ends
+  // (only rows of 8 were taken whole before, any other as 4, 2 or 1 sites: D_bb of 12 fields,
+  // L_s = 12, 6 x 16^3 294 -> 216 us, 10^3 x 20 244 -> 170, 22 x 8 x 8 x 16 270 -> 187; always
+  // across row ends D_bb of 8^3 x 16 takes 21.0 us instead of 18.3).  FP64 / FP32: one until
+  // the chip is full, then up to 16, which repay the load of the matrices.
+  auto cap = [&](size_t sites) { return tile || sites >= 32768 ? 8u : (sites >= 8192 ? 4u : 1u); };
   auto sites_per_wave = [&](size_t sites) {
     unsigned spw = 1;
     if (S::prec == DWA_BF16) {
-      const unsigned cap = tile || sites >= 32768 ? 8 : (sites >= 8192 ? 4 : 1);
-      while (2 * spw <= cap && a.geo.Lxh % (2 * spw) == 0) spw *= 2;
+      spw = cap(sites);
+      for (unsigned d = spw; d >= 3; --d)
+        if (a.geo.Lxh % d == 0) return d;
+      if (a.geo.Lxh <= 2 && sites < 32768 && spw > a.geo.Lxh) spw = a.geo.Lxh;
     } else if (tile) {
       spw = NSB / NW;
     } else {
@@ -926,34 +930,57 @@ int launch_wave_hop_p(dwa_ctx* ctx, const WaveOp& op, int* nparts) {
     }
     return spw;
   };
-  a.spw = sites_per_wave(size_t(a.Vh) * ny);
   // Norms are grouped by the lattice alone, so that a batch's field sums them as its own solve
-  // does (both are powers of two).  The further sums of a wave cost a batch 0 to 4% of an
-  // iteration (BF16, 12 fields of 8^3 x 16, L_s = 12: 244 -> 251 us; FP64, L_s = 9: 613 ->
-  // 628), where giving every wave the sites of the single solve costs up to 10 (257, 633).
+  // does.  Its updates then sum as many terms as the single solve's, which costs a batch 0 to
+  // 4% of an iteration (BF16, 12 fields of 8^3 x 16, L_s = 12: 244 -> 251 us; FP64, L_s = 9:
+  // 613 -> 628) and up to 11 where few slices meet many sites (FP32, 12 of 12^3 x 24, L_s = 5:
+  // 1615 -> 1795); giving every wave the sites of the single solve costs up to 10 (257, 633).
+  a.spw = sites_per_wave(size_t(a.Vh) * ny);
   a.spg = sites_per_wave(a.Vh);
+  if (a.spw % a.spg != 0) a.spw = cap(size_t(a.Vh) * ny) / a.spg * a.spg;
   a.nsum = (a.Vh + NW * a.spg - 1) / (NW * a.spg);
+  // The walk: each XCD's range a group of Lz / 8 z-planes, walked in t, where that is two
+  // planes or more (against plain order: 16^3 x 32, solves 0 to 2% and D_bb 0 to 5% less time;
+  // 6 x 16^3 and 16^4 the same within 1%); of a single plane the neighbours in z are all
+  // another XCD's (8^4 and 8^3 x 16: D_bb 0 to 12% more, solves 0 to 3).  The tiled store takes plain
+  // order unless a plane is whole blocks, whose sites must be consecutive.
+  if (ctx->dims[2] % 8 == 0 && ctx->dims[2] >= 16 && !(tile && (a.geo.Lxh * a.geo.Ly) % (NW * a.spw) != 0)) {
+    a.geo.ZB = (unsigned)ctx->dims[2] / 8;
+    a.geo.mZB = ctx->wgeo_mzdom;
+  }
   const unsigned nblk = (a.Vh + NW * a.spw - 1) / (NW * a.spw);
   const dim3 grid(nblk, ny);
   const size_t shm = tile ? size_t(12) * a.Ls * (NSB + 1) * EB : 0;
   if (nparts) *nparts = int(a.nsum);
-#define DWA_WAVE(SPLIT, POST, INSM, OUTL) \
-  hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL>), grid, dim3(256), shm, ctx->stream, a)
+  const bool cross = a.geo.Lxh % a.spw != 0;
+#define DWA_WAVE(SPLIT, POST, INSM, OUTL)                                                                       \
+  if (S::prec == DWA_BF16 && cross)                                                                              \
+    hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL, S::prec == DWA_BF16>), grid, dim3(256), shm, \
+                       ctx->stream, a);                                                                          \
+  else                                                                                                           \
+    hipLaunchKernelGGL((wave_hop_kernel<S, SPLIT, POST, INSM, OUTL, false>), grid, dim3(256), shm, ctx->stream, a)
   if (split) {
     if (op.post || op.out_soa) {
       set_error("wave hop: unsupported combination");
       return DWA_EINVAL;
     }
-    if (op.in_soa) DWA_WAVE(true, false, false, 1);
-    else DWA_WAVE(true, false, true, 1);
+    if (op.in_soa) {
+      DWA_WAVE(true, false, false, 1);
+    } else {
+      DWA_WAVE(true, false, true, 1);
+    }
   } else {
     if (!op.post || op.in_soa) {
       set_error("wave hop: unsupported combination");
       return DWA_EINVAL;
     }
-    if (tile) DWA_WAVE(false, true, true, 2);
-    else if (op.out_soa) DWA_WAVE(false, true, true, 0);
-    else DWA_WAVE(false, true, true, 1);
+    if (tile) {
+      DWA_WAVE(false, true, true, 2);
+    } else if (op.out_soa) {
+      DWA_WAVE(false, true, true, 0);
+    } else {
+      DWA_WAVE(false, true, true, 1);
+    }
   }
 #undef DWA_WAVE
   return hip_fail(hipGetLastError(), "wave hop launch");

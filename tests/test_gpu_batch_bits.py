@@ -10,7 +10,9 @@ pytestmark = pytest.mark.gpu
 # lattices of the wave hop and of the site blocks; batches on both sides of the sites from
 # which a hop without norms gives a wave several sites (32768; BF16 8192)
 CASES = [((4, 4, 4, 4), 8, 12, "f64"), ((8, 8, 8, 16), 9, 9, "f64"), ((8, 4, 4, 8), 12, 3, "f64"),
-         ((8, 8, 8, 8), 12, 3, "f64"), ((8, 8, 8, 16), 9, 9, "f32"), ((8, 8, 8, 16), 12, 6, "bf16")]
+         ((8, 8, 8, 8), 12, 3, "f64"), ((8, 8, 8, 16), 9, 9, "f32"), ((8, 8, 8, 16), 12, 6, "bf16"),
+         ((8, 4, 8, 8), 9, 70, "f64"), ((8, 4, 8, 8), 7, 140, "f32"), ((6, 4, 8, 8), 9, 70, "bf16"),
+         ((10, 4, 4, 6), 9, 80, "bf16"), ((22, 2, 4, 4), 12, 110, "bf16"), ((12, 8, 12, 16), 9, 4, "bf16")]
 
 
 
