@@ -375,31 +375,52 @@ inline int hop_sites_per_block(const dwa_ctx* ctx, int prec) {
 }
 
 // Which D_bb and D_bb^dag the wave hop runs: where it is the faster one (16^3 x 32 down to
-// 4^4, all three precisions, one field and twelve).  Not for dense matrices.
-//   L_s without kernels of its own in hop_mix_kernel: always (D_bb of 12^3 x 24, L_s = 9:
-//     FP32 117 -> 84 us, FP64 254 -> 132; L_s = 5: 89 -> 81, 162 -> 121).
+// 4^4, all three precisions, one field and twelve; four from 16^4 on).  Not for dense matrices.
+//   L_s without kernels of its own in hop_mix_kernel.  A wave pays for 16 slices whatever L_s,
+//     the generic kernel for those there are: always in BF16 (D_bb of 16^3 x 32, L_s = 2: 81
+//     -> 42 us) and from L_s = 7 on (12^3 x 24, L_s = 9: FP32 117 -> 84, FP64 254 -> 132);
+//     below, D_bb of FP32 while a call is small (L_s = 2: 12 fields of 8^4 4% slower, of
+//     6^3 x 12 7% faster, 16^3 x 32 15% slower; L_s = 5: 9% slower from 128k sites on, 7% faster
+//     at 120k), and D_bb of FP64 at L_s = 2, 3 up to 24576 sites of the lattice (16^3 x 32,
+//     L_s = 3 16% slower).
 //   Other L_s of FP32 and FP64: the smallest lattices only.  Two or four launches there cost
 //     their latency, and a wave's chain of 16 lanes x 4 slices is shorter than a thread's
 //     sweeps (CGLS iteration at 4^3 x 8, L_s = 8: FP64 67 -> 41 us); on a full chip the sweeps
 //     do less work (D_bb of 16^3 x 32, L_s = 10: FP32 168 us against 238).
 //   BF16: the matrix cores do the hop as well, so the lines lie higher.  D_bb at L_s >= 12:
 //     while the input, its site-major copy, the red field and the output fit the 256 MB
-//     Infinity Cache (16^3 x 32, L_s = 16, one field 111 -> 103 us, L_s = 12 97 -> 89; two
-//     fields 233 against 238; twelve of 12^3 x 24, L_s = 12 389 against 414).
+//     Infinity Cache, or 3/4 of it where an x row has four sites or fewer (D_bb of 16^3 x 32,
+//     L_s = 16: one buffer 110 -> 102 us, four in turn 113.6 -> 113.0; D_bb and D_bb^dag in turn,
+//     new buffers each pass, 232 -> 229; L_s = 12 97 -> 88, in turn 97 -> 93; 12 fields of
+//     8 x 12^2 x 16, L_s = 12, 110592 sites 141 -> 152).
 // Solvers keep their fields site-major (no premixed fields, elementwise updates).  Their rule
 // takes the lattice alone, so that a field of a batch runs the kernels of its own solve, bit
-// for bit; it is set where twelve fields are no slower either (iteration at 1024 sites per
-// parity, L_s = 8, FP32: one field 69 -> 43 us, twelve 120 -> 130; L_s = 12: 72 -> 46, 157
-// -> 140).  D_bb of the caller's SoA fields pays for its relayout and is chosen by all sites
-// of the call.
+// for bit, and the lines are where an iteration of twelve fields is no slower than the
+// site-block hop's: one field would gain on to about 4000 sites (at 512 sites, L_s = 8, FP64:
+// one field 0.70 of the time, twelve 1.09; FP32 0.71 and 1.08; at 256 0.70 and 0.90).  D_bb of
+// the caller's SoA fields pays for its relayout and is chosen by all sites of the call.
 constexpr int kWaveMinLs = 2, kWaveMaxLs = 16;
 inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
+  constexpr long long always = LLONG_MAX;
   const int Ls = ctx->Ls;
   if (Ls < kWaveMinLs || Ls > kWaveMaxLs || !ctx->wave_geo_ok) return 0;
-  if (!hop_specialised(Ls, false) && !hop_even(Ls, prec, false)) return LLONG_MAX;
-  if (prec == DWA_BF16)
-    return soa ? (Ls >= 12 ? (1LL << 28) / (4 * 48 * Ls) : (Ls == 8 ? 6144 : 4096)) : (Ls >= 12 ? LLONG_MAX : (Ls == 8 ? 2048 : 1024));
-  return soa ? 1024 : (Ls >= 10 ? 1024 : (Ls >= 6 ? 512 : 256));
+  if (!hop_specialised(Ls, false) && !hop_even(Ls, prec, false)) {
+    if (prec == DWA_F64 && Ls <= 3 && soa) return ctx->Vh <= 24576 ? always : 0;
+    if (prec == DWA_F32 && Ls <= 3) return soa ? 16384 : 1536;
+    if (prec == DWA_F32 && Ls == 5) return soa ? 65536 : 12288;
+    return always;
+  }
+  if (prec == DWA_BF16) {
+    if (Ls >= 12) {
+      const long long cache = ctx->dims[0] > 8 ? 1LL << 28 : 3LL << 26;
+      return soa ? cache / (4 * 48 * Ls) : always;
+    }
+    if (Ls == 8) return soa ? 6144 : 2048;
+    return soa ? 4096 : 1024;
+  }
+  if (soa) return 1024;
+  if (prec == DWA_F64) return Ls >= 14 ? 1024 : 320;
+  return Ls >= 12 ? 1024 : 384;
 }
 inline bool wave_ok(const dwa_ctx* ctx, int prec, bool soa, long long sites) {
   return sites <= wave_max_sites(ctx, prec, soa) && !use_dense(ctx, prec) && ctx->prec[prec].wlinks;

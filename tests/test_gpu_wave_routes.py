@@ -59,7 +59,7 @@ def test_tiled_batches(dims, Ls, n):
 
 @pytest.mark.parametrize("prec", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("dims,Ls,n", [((4, 2, 16, 2), 9, 3), ((6, 2, 16, 4), 7, 3), ((2, 4, 32, 2), 13, 2),
-                                       ((16, 2, 2, 4), 3, 260), ((6, 2, 16, 4), 3, 180)])
+                                       ((16, 2, 2, 4), 7, 260), ((6, 2, 16, 4), 7, 180)])
 def test_walk_and_sites_per_wave(dims, Ls, n, prec):
     """z-plane groups, and batches of 32768 sites and more, whose waves take several sites
     each: D_bb and D_bb^dag against the oracle, the batch bit for bit the single call."""
@@ -112,3 +112,58 @@ def test_even_ls_solvers(Ls, inner, delta):
         for a in (y, ys[k]):
             assert float(torch.linalg.vector_norm(a - g)) <= 1e-8 * float(torch.linalg.vector_norm(g))
     ctx.close()
+
+
+# (lattice, L_s, precision, fields, whether the wave hop runs): both sides of the lines of
+# dwa_internal.h's wave_max_sites
+DBB_LINES = [((8, 8, 8, 8), 2, "f32", 8, True), ((8, 8, 8, 8), 3, "f32", 9, False), ((8, 8, 8, 8), 5, "f32", 32, True),
+             ((8, 8, 8, 8), 4, "f64", 1, False), ((8, 8, 8, 8), 5, "f32", 33, False), ((8, 8, 8, 8), 7, "f32", 33, True),
+             ((16, 8, 16, 24), 3, "f64", 1, True), ((16, 16, 16, 16), 3, "f64", 1, False),
+             ((16, 16, 16, 16), 5, "f64", 1, True), ((16, 16, 16, 16), 2, "bf16", 1, True),
+             ((8, 8, 8, 8), 12, "bf16", 42, True), ((8, 8, 8, 8), 12, "bf16", 43, False)]
+SOLVE_LINES = [((6, 6, 6, 12), 3, "f32", True), ((8, 8, 8, 8), 3, "f32", False), ((8, 8, 8, 8), 3, "f64", True),
+               ((4, 4, 4, 10), 8, "f64", True), ((4, 4, 4, 12), 8, "f64", False), ((8, 4, 4, 8), 12, "f64", False),
+               ((8, 4, 8, 8), 14, "f64", True), ((6, 4, 4, 8), 10, "f32", True), ((4, 4, 4, 14), 10, "f32", False),
+               ((8, 4, 8, 8), 12, "f32", True), ((8, 8, 8, 8), 5, "f32", True), ((8, 8, 8, 8), 8, "bf16", True),
+               ((8, 8, 8, 10), 8, "bf16", False), ((8, 8, 8, 10), 12, "bf16", True)]
+
+
+def both_routes(monkeypatch, dims, Ls, batch, call):
+    U = synth.su3_field(dims, 0.5, 3)
+    out = []
+    for off in (False, True):
+        if off:
+            monkeypatch.setenv("DWA_NO_WAVE_HOP", "1")
+        ctx = context(dims, Ls, U, batch)
+        gen = torch.Generator(device="cuda").manual_seed(3)
+        out.append(call(ctx, gen).clone())
+        ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("dims,Ls,prec,n,wave", DBB_LINES)
+def test_lines_of_dbb(dims, Ls, prec, n, wave, monkeypatch):
+    """The two hops round differently, so equal bits are the site-block hop's."""
+    print(f"[gpu] D_bb line {dims} Ls={Ls} {prec} x{n}", flush=True)
+
+    def call(ctx, gen):
+        x = torch.stack([ctx.half_field(prec) for _ in range(n)]).contiguous()
+        x.copy_(torch.randn(x.shape, dtype=torch.float32 if prec == "bf16" else x.dtype, device="cuda", generator=gen))
+        return ctx.apply_Dbb_batch(x, prec) if n > 1 else ctx.apply_Dbb(x[0], prec)
+
+    a, b = both_routes(monkeypatch, dims, Ls, n if n > 1 else 0, call)
+    assert torch.equal(a, b) == (not wave)
+
+
+@pytest.mark.parametrize("dims,Ls,inner,wave", SOLVE_LINES)
+def test_lines_of_solvers(dims, Ls, inner, wave, monkeypatch):
+    """A few iterations and one correction: bits as above."""
+    print(f"[gpu] solve line {dims} Ls={Ls} {inner}", flush=True)
+
+    def call(ctx, gen):
+        rhs = ctx.half_field("f64")
+        rhs.copy_(torch.randn(rhs.shape, dtype=rhs.dtype, device="cuda", generator=gen))
+        return ctx.cgne_solve(rhs, tol=1e-12, inner_prec=inner, delta=1e-3, maxiter=8, check_every=8)[0]
+
+    a, b = both_routes(monkeypatch, dims, Ls, 0, call)
+    assert torch.equal(a, b) == (not wave)
