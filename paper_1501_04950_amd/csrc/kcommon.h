@@ -801,20 +801,20 @@ __device__ __forceinline__ void st_stream(typename S::elem* p, size_t i, cpx<typ
   }
 }
 
-// The updates run one thread per (site, colour-spin component): the first half of the grid
-// takes the upper chirality, the second the lower (uniform per block), so that a thread has
-// one row of slices to load and mix, and r and q (z and p) of the row are on their way while
-// the partials are summed: on a small lattice there are few blocks, and an update is a chain of
-// memory trips.  CGLS iteration at 8^3 x 16, L_s = 12, one field: FP32 82 -> 71 us, FP64 99 ->
-// 87 (update 1 17 -> 12.5 us, update 2 12.5 -> 7); twelve fields 2 to 3% less, and the same on
-// a full chip, where both are memory bound (FP32, 12 fields of 8^4, L_s = 8: 5.6 TB/s).  Blocks
-// of 64 and 128 threads were no faster.
+// The updates run one thread per site, colour and spin of a chirality.  With HALF a thread takes
+// one chirality: the first half of the grid the upper one, the second the lower (uniform per
+// block).  The thread's row of slices is on its way while the partials are summed: on a small
+// lattice there are few blocks, and an update is a chain of memory trips.  CGLS iteration at
+// 8^3 x 16, L_s = 12, one field: FP32 82 -> 71 us, FP64 99 -> 87 (update 1 17 -> 12.5 us, update
+// 2 12.5 -> 7); twelve fields 2 to 3% less.  Blocks of 64 and 128 threads were no faster.
+// Without HALF it takes one after the other, in half as many blocks, each of which sums all the
+// hops' partials: update_half says where that is the faster one.
 #define DWA_UPDATE_THREAD                                                                    \
-  const unsigned half_grid = gridDim.x / 2;                                                  \
-  const int ch = blockIdx.x < half_grid ? 0 : 1;                                             \
-  const unsigned t = (blockIdx.x - (ch ? half_grid : 0u)) * blockDim.x + threadIdx.x;        \
+  const unsigned half_grid = HALF ? gridDim.x / 2 : gridDim.x;                               \
+  const int ch0 = blockIdx.x < half_grid ? 0 : 1;                                            \
+  const unsigned t = (blockIdx.x - (ch0 ? half_grid : 0u)) * blockDim.x + threadIdx.x;       \
   const bool live = t < 6u * Vh;                                                             \
-  const unsigned c6 = live ? t / Vh : 0u, site = live ? t % Vh : 0u, comp = unsigned(ch) * 6u + c6
+  const unsigned c6 = live ? t / Vh : 0u, site = live ? t % Vh : 0u
 
 // CGLS update 1: x += a p ; r -= a q ; |r|^2 ; w = (g5 I^-T G^-1) r.
 // With qparts (the nq block partials of |q|^2 per field), every block sums them itself
@@ -823,7 +823,7 @@ __device__ __forceinline__ void st_stream(typename S::elem* p, size_t i, cpx<typ
 // this update is saved.  Otherwise a comes from the scalars.  With zparts as well (the
 // nz partials of |z|^2 of the current z = A^dag r), gamma = |z|^2 is summed here too
 // and block 0 stores it (update 2 of this step divides by it).
-template <typename S, int LS, bool DENSE, int PK>
+template <typename S, int LS, bool DENSE, int PK, bool HALF>
 __global__ void __launch_bounds__(256) cg_update1_kernel(typename XAcc<S>::type::elem* __restrict__ x,
                                                          typename S::elem* __restrict__ r,
                                                          typename S::elem* __restrict__ w,
@@ -851,16 +851,17 @@ __global__ void __launch_bounds__(256) cg_update1_kernel(typename XAcc<S>::type:
   // length stays in memory)
   constexpr bool AHEAD = LS > 0;
   cpx<R> rv[LSM], qv[AHEAD ? LSM : 1];
-  if constexpr (AHEAD) {
-    if (live) {
+  auto load = [&](int ch) {
+    if (AHEAD && live) {
 #pragma unroll
       for (int j = 0; j < LSM; ++j) {
-        const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
-        qv[j] = ld_stream<S>(q, idx);
+        const size_t idx = (size_t(j) * 12 + ch * 6 + c6) * Vh + site;
+        qv[AHEAD ? j : 0] = ld_stream<S>(q, idx);
         rv[j] = ld<S>(r, idx);
       }
     }
-  }
+  };
+  load(ch0);
   double ad;
   if (qparts) {
     const double qq = sum_partials_block(qparts + size_t(blockIdx.y) * nq, nq);
@@ -880,31 +881,37 @@ __global__ void __launch_bounds__(256) cg_update1_kernel(typename XAcc<S>::type:
   if (live) {
     const R a = (R)ad;
 #pragma unroll
-    for (int j = 0; j < LSM; ++j)
-      if (j < Ls) {
-        const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
-        using SX = typename XAcc<S>::type;
-        cpx<R> xv = ld_stream<SX>(x, idx), rr, qq;
-        const cpx<R> pv = ld<S>(p, idx);
-        if constexpr (AHEAD) {
-          qq = qv[j];
-          rr = rv[j];
-        } else {
-          qq = ld_stream<S>(q, idx);
-          rr = ld<S>(r, idx);
-        }
-        xv = xv + a * pv;
-        rr = rr - a * qq;
-        st_stream<SX>(x, idx, xv);
-        st<S>(r, idx, rr);
-        rv[j] = as_stored<S>(rr);  // premix the value as stored
-        nrm += (double)norm2(rv[j]);
-      }
-    if (ch == 0) apply_mix<R, LSM, PK, 0, DENSE>(rv, Ls, P);
-    else apply_mix<R, LSM, PK, 1, DENSE>(rv, Ls, P);
+    for (int k = 0; k < (HALF ? 1 : 2); ++k) {
+      const int ch = HALF ? ch0 : k;
+      const unsigned comp = unsigned(ch) * 6u + c6;
+      if (k) load(ch);
 #pragma unroll
-    for (int i = 0; i < LSM; ++i)
-      if (i < Ls) st<S>(w, (size_t(i) * 12 + comp) * Vh + site, rv[i]);
+      for (int j = 0; j < LSM; ++j)
+        if (j < Ls) {
+          const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
+          using SX = typename XAcc<S>::type;
+          cpx<R> xv = ld_stream<SX>(x, idx), rr, qq;
+          const cpx<R> pv = ld<S>(p, idx);
+          if constexpr (AHEAD) {
+            qq = qv[j];
+            rr = rv[j];
+          } else {
+            qq = ld_stream<S>(q, idx);
+            rr = ld<S>(r, idx);
+          }
+          xv = xv + a * pv;
+          rr = rr - a * qq;
+          st_stream<SX>(x, idx, xv);
+          st<S>(r, idx, rr);
+          rv[j] = as_stored<S>(rr);  // premix the value as stored
+          nrm += (double)norm2(rv[j]);
+        }
+      if (ch == 0) apply_mix<R, LSM, PK, 0, DENSE>(rv, Ls, P);
+      else apply_mix<R, LSM, PK, 1, DENSE>(rv, Ls, P);
+#pragma unroll
+      for (int i = 0; i < LSM; ++i)
+        if (i < Ls) st<S>(w, (size_t(i) * 12 + comp) * Vh + site, rv[i]);
+    }
   }
   if (partials) block_sum_to(nrm, &partials[blockIdx.y * gridDim.x + blockIdx.x]);
 }
@@ -914,7 +921,7 @@ __global__ void __launch_bounds__(256) cg_update1_kernel(typename XAcc<S>::type:
 // beta = |z|^2 / gamma; block 0 stores zz, beta and the breakdown flag.  gamma keeps
 // the previous |z|^2 until the next update 1 replaces it.  Otherwise beta comes from
 // the scalars.
-template <typename S, int LS, bool DENSE, int PK>
+template <typename S, int LS, bool DENSE, int PK, bool HALF>
 __global__ void __launch_bounds__(256) cg_update2_kernel(typename S::elem* __restrict__ p,
                                                          typename S::elem* __restrict__ u,
                                                          const typename S::elem* __restrict__ z,
@@ -934,16 +941,17 @@ __global__ void __launch_bounds__(256) cg_update2_kernel(typename S::elem* __res
   }
   constexpr bool AHEAD = LS > 0;  // as in update 1
   cpx<R> pv[LSM], zv[AHEAD ? LSM : 1];
-  if constexpr (AHEAD) {
-    if (live) {
+  auto load = [&](int ch) {
+    if (AHEAD && live) {
 #pragma unroll
       for (int j = 0; j < LSM; ++j) {
-        const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
-        zv[j] = ld_stream<S>(z, idx);
+        const size_t idx = (size_t(j) * 12 + ch * 6 + c6) * Vh + site;
+        zv[AHEAD ? j : 0] = ld_stream<S>(z, idx);
         pv[j] = ld<S>(p, idx);
       }
     }
-  }
+  };
+  load(ch0);
   double bd;
   if (zparts) {
     const double zz = sum_partials_block(zparts + size_t(blockIdx.y) * nz, nz);
@@ -960,20 +968,26 @@ __global__ void __launch_bounds__(256) cg_update2_kernel(typename S::elem* __res
   if (!live) return;
   const R beta = (R)bd;
 #pragma unroll
-  for (int j = 0; j < LSM; ++j)
-    if (j < Ls) {
-      const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
-      cpx<R> v;
-      if constexpr (AHEAD) v = zv[j] + beta * pv[j];
-      else v = ld_stream<S>(z, idx) + beta * ld<S>(p, idx);
-      st<S>(p, idx, v);
-      pv[j] = as_stored<S>(v);
-    }
-  if (ch == 0) apply_mix<R, LSM, PK, 0, DENSE>(pv, Ls, P);
-  else apply_mix<R, LSM, PK, 1, DENSE>(pv, Ls, P);
+  for (int k = 0; k < (HALF ? 1 : 2); ++k) {
+    const int ch = HALF ? ch0 : k;
+    const unsigned comp = unsigned(ch) * 6u + c6;
+    if (k) load(ch);
 #pragma unroll
-  for (int i = 0; i < LSM; ++i)
-    if (i < Ls) st<S>(u, (size_t(i) * 12 + comp) * Vh + site, pv[i]);
+    for (int j = 0; j < LSM; ++j)
+      if (j < Ls) {
+        const size_t idx = (size_t(j) * 12 + comp) * Vh + site;
+        cpx<R> v;
+        if constexpr (AHEAD) v = zv[j] + beta * pv[j];
+        else v = ld_stream<S>(z, idx) + beta * ld<S>(p, idx);
+        st<S>(p, idx, v);
+        pv[j] = as_stored<S>(v);
+      }
+    if (ch == 0) apply_mix<R, LSM, PK, 0, DENSE>(pv, Ls, P);
+    else apply_mix<R, LSM, PK, 1, DENSE>(pv, Ls, P);
+#pragma unroll
+    for (int i = 0; i < LSM; ++i)
+      if (i < Ls) st<S>(u, (size_t(i) * 12 + comp) * Vh + site, pv[i]);
+  }
 }
 
 template <typename S>
@@ -1274,6 +1288,19 @@ int launch_smix_p(dwa_ctx* ctx, int mix, void* out, const void* in, const void* 
   return hip_fail(hipGetLastError(), "smix kernel launch");
 }
 
+// Whether an update's thread takes one chirality.  FP64 always (at 16^3 x 32 0 to 1% of an
+// iteration faster than both, L_s = 4 to 12).  FP32 and BF16 up to 32768 sites, BF16 at L_s = 4
+// to 4096: on a full chip the partials that twice the blocks sum are read from L2 for longer than
+// the fields (16^3 x 32: update 1 of BF16 22.6 -> 25.9 us at L_s = 4, 39.3 -> 42.3 at 8, of
+// FP32 32.1 -> 34.3 and 57.6 -> 61.6; update 2 11.0 -> 13.3, 17.8 -> 19.0, 19.1 -> 21.4, but at
+// L_s = 8 of FP32 38.3 -> 35.9), which more slices repay in FP32.
+template <typename S>
+bool update_half(const dwa_ctx* ctx, int update) {
+  if (S::prec == DWA_F64) return true;
+  if (S::prec == DWA_F32 && ctx->Ls >= (update == 1 ? 9 : 8)) return true;
+  return ctx->Vh <= (S::prec == DWA_BF16 && ctx->Ls <= 4 ? 4096 : 32768);
+}
+
 template <typename S>
 int launch_update1_p(dwa_ctx* ctx, void* x, void* r, void* w, const void* p, const void* q,
                      DevScalars* s, double* partials, int* nblocks, bool adj, int nrhs,
@@ -1281,19 +1308,22 @@ int launch_update1_p(dwa_ctx* ctx, void* x, void* r, void* w, const void* p, con
   using E = typename S::elem;
   using EX = typename XAcc<S>::type::elem;
   const unsigned Vh = (unsigned)ctx->Vh;
-  const int grid = (int)(2 * ((6u * Vh + 255) / 256));
+  const bool half = update_half<S>(ctx, 1);
+  const int grid = (int)((half ? 2 : 1) * ((6u * Vh + 255) / 256));
   // w is the premixed input of the operator applied to r next: D_bb^dag (normal CGLS)
   // or, for CGLS on D_bb^dag, D_bb
   const MixTables T = mix_tables<S>(ctx, adj ? MIX_BG : MIX_G5_IINVT_GINV);
-#define DWA_U1(LSV, DV)                                                                          \
-  if (adj) {                                                                                     \
-    hipLaunchKernelGGL((cg_update1_kernel<S, LSV, DV, MIX_BG>), dim3(grid, nrhs), dim3(256), 0,   \
-                       ctx->stream, (EX*)x, (E*)r, (E*)w, (const E*)p, (const E*)q, s, T,         \
-                       ctx->Ls, Vh, partials, qparts, nq, zparts, nz);                           \
-  } else {                                                                                       \
-    hipLaunchKernelGGL((cg_update1_kernel<S, LSV, DV, MIX_G5_IINVT_GINV>), dim3(grid, nrhs), dim3(256), \
-                       0, ctx->stream, (EX*)x, (E*)r, (E*)w, (const E*)p, (const E*)q, s, T,      \
-                       ctx->Ls, Vh, partials, qparts, nq, zparts, nz);                                                   \
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid, nrhs), dim3(256), 0, ctx->stream, (EX*)x, (E*)r, (E*)w, (const E*)p,
+                       (const E*)q, s, T, ctx->Ls, Vh, partials, qparts, nq, zparts, nz);
+  };
+#define DWA_U1(LSV, DV)                                                                                          \
+  if (half) {                                                                                                    \
+    if (adj) run(cg_update1_kernel<S, LSV, DV, MIX_BG, true>);                                                   \
+    else run(cg_update1_kernel<S, LSV, DV, MIX_G5_IINVT_GINV, true>);                                            \
+  } else if constexpr (S::prec != DWA_F64) {                                                                     \
+    if (adj) run(cg_update1_kernel<S, LSV, DV, MIX_BG, false>);                                                  \
+    else run(cg_update1_kernel<S, LSV, DV, MIX_G5_IINVT_GINV, false>);                                           \
   }
   DWA_LS_DISPATCH(ctx->Ls, use_dense(ctx, S::prec), DWA_U1)
 #undef DWA_U1
@@ -1306,18 +1336,22 @@ int launch_update2_p(dwa_ctx* ctx, void* p, void* u, const void* z, DevScalars* 
                      int nrhs, const double* zparts, int nz) {
   using E = typename S::elem;
   const unsigned Vh = (unsigned)ctx->Vh;
-  const int grid = (int)(2 * ((6u * Vh + 255) / 256));
+  const bool half = update_half<S>(ctx, 2);
+  const int grid = (int)((half ? 2 : 1) * ((6u * Vh + 255) / 256));
   // u is the premixed input of the operator applied to p next: D_bb (normal CGLS) or,
   // for CGLS on D_bb^dag, D_bb^dag
   const MixTables T = mix_tables<S>(ctx, adj ? MIX_G5_IINVT_GINV : MIX_BG);
-#define DWA_U2(LSV, DV)                                                                        \
-  if (adj) {                                                                                   \
-    hipLaunchKernelGGL((cg_update2_kernel<S, LSV, DV, MIX_G5_IINVT_GINV>), dim3(grid, nrhs),     \
-                       dim3(256), 0, ctx->stream, (E*)p, (E*)u, (const E*)z, s, T, ctx->Ls, Vh,   \
-                       zparts, nz);                                                            \
-  } else {                                                                                     \
-    hipLaunchKernelGGL((cg_update2_kernel<S, LSV, DV, MIX_BG>), dim3(grid, nrhs), dim3(256), 0, \
-                       ctx->stream, (E*)p, (E*)u, (const E*)z, s, T, ctx->Ls, Vh, zparts, nz);  \
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid, nrhs), dim3(256), 0, ctx->stream, (E*)p, (E*)u, (const E*)z, s, T, ctx->Ls,
+                       Vh, zparts, nz);
+  };
+#define DWA_U2(LSV, DV)                                                                                          \
+  if (half) {                                                                                                    \
+    if (adj) run(cg_update2_kernel<S, LSV, DV, MIX_G5_IINVT_GINV, true>);                                        \
+    else run(cg_update2_kernel<S, LSV, DV, MIX_BG, true>);                                                       \
+  } else if constexpr (S::prec != DWA_F64) {                                                                     \
+    if (adj) run(cg_update2_kernel<S, LSV, DV, MIX_G5_IINVT_GINV, false>);                                       \
+    else run(cg_update2_kernel<S, LSV, DV, MIX_BG, false>);                                                      \
   }
   DWA_LS_DISPATCH(ctx->Ls, use_dense(ctx, S::prec), DWA_U2)
 #undef DWA_U2

@@ -63,3 +63,27 @@ def test_serial_launches_give_the_batch(inner, Ls, what, monkeypatch):
     assert [s["iters"] for s in st[0]] == [t["iters"] for t in tt[0]]
     assert torch.equal(xs[0], ys[0])
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,Ls,inner", [((4, 8, 16, 20), 4, "bf16"), ((4, 16, 32, 34), 8, "f32"), ((2, 16, 32, 66), 8, "bf16")])
+def test_updates_of_both_chiralities(dims, Ls, inner):
+    """Lattices whose CG updates take both chiralities in a thread: the solution against that
+    of the dense kernels, and a zero source beside it in a batch."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[gpu] updates {dims} Ls={Ls} {inner}", flush=True)
+    ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
+    ctx.set_links(torch.from_numpy(synth.su3_field(dims, 0.3, 7)).cuda())
+    ctx.reserve_batch(2)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rhs = torch.zeros((2,) + tuple(ctx.half_field("f64").shape), dtype=torch.complex128, device="cuda")
+    rhs[0].copy_(torch.randn(rhs[0].shape, dtype=rhs.dtype, device="cuda", generator=gen))
+    o = dict(tol=1e-9, inner_prec=inner, delta=0.1, check_every=5, maxiter=2000)
+    x, s, rc = ctx.cgne_solve(rhs[0].contiguous(), **o)
+    xs, _, rb = dwa.cgne_solve_batch([(ctx, rhs)], **o)
+    ctx.set_tuning(inner, 8, "slab", 1, True)
+    g, _, rg = ctx.cgne_solve(rhs[0].contiguous(), **o)
+    assert rc == rb == rg == dwa.DWA_OK and not xs[0][1].abs().any()
+    n = torch.linalg.vector_norm(g)
+    assert torch.linalg.vector_norm(x - g) <= 1e-7 * n and torch.linalg.vector_norm(xs[0][0] - g) <= 1e-7 * n
+    ctx.close()
