@@ -1507,9 +1507,10 @@ int dwa_create(dwa_ctx** out, const dwa_params* p, void* stream) {
   for (int pr = 0; pr < 3; ++pr)
     if ((rc = hip_fail(hipMalloc(&ctx->prec[pr].links, elem_bytes(pr) * 2 * 4 * 9 * Vh), "alloc links")))
       return fail(rc);
-  // gathered links where the wave hop can run (also after a change of tuning or alpha)
+  // gathered links where the wave hop can run, also after a change of tuning (a context
+  // created with dense matrices stays without)
   for (int pr = 0; pr < 3; ++pr)
-    if (Vh <= std::max(wave_max_sites(ctx, pr, false), wave_max_sites(ctx, pr, true)) &&
+    if (!ctx->dense_mix && Vh <= std::max(wave_max_sites(ctx, pr, false), wave_max_sites(ctx, pr, true)) &&
         (rc = hip_fail(hipMalloc(&ctx->prec[pr].wlinks, elem_bytes(pr) * 2 * 72 * Vh), "alloc links")))
       return fail(rc);
   for (int i = 0; i < W64_COUNT; ++i)

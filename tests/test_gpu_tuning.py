@@ -91,3 +91,26 @@ def test_wave_solve_does_not_depend_on_the_order():
         xs.append(ctx.cgne_solve(rhs, tol=1e-12, maxiter=40, check_every=8)[0].clone())
     assert torch.equal(xs[0], xs[1]) and torch.equal(xs[0], xs[2])
     ctx.close()
+
+
+@pytest.mark.parametrize("variable", ["DWA_DENSE_MIX", "DWA_NO_WAVE_HOP"])
+def test_no_gathered_links_without_the_wave_hop(variable, monkeypatch):
+    """A context that never runs the wave hop holds no second copy of the links: 144 numbers
+    per site of a parity in FP64 and BF16 (FP32 runs it on smaller lattices at this L_s)."""
+    dims, Ls = (16, 16, 16, 16), 3
+    need = 144 * 16**4 // 2 * (16 + 4)
+
+    def held():
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        ctx = dwa.Context(dims, Ls, -1.8, 0.05, 0.8, 1.5, 0.5)
+        used = before - torch.cuda.mem_get_info()[0]
+        ctx.close()
+        return used
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    held()  # (first-use allocations)
+    full = held()
+    monkeypatch.setenv(variable, "1")
+    assert full - held() >= 0.9 * need
