@@ -1,5 +1,5 @@
 // Wave-per-site hop kernels of libdwa: one wavefront computes one site on all slices
-// (L_s = 8 .. 16, one slice per lane group), with the fifth-dimension matrices before and
+// (L_s = 2 .. 16: there is room for 16 slices), with the fifth-dimension matrices before and
 // after the hop applied together on the matrix cores.
 //
 // Field layout of these kernels ("site-major"): element (site, colour, s, spin) of a half
@@ -368,15 +368,16 @@ __device__ __forceinline__ void wave_hop_bf16(const uint32_t* tab, const WaveLin
   }
 }
 
-// out = M_D D + M_T T (+ post), D and T the two parts of the hop (see wave_hop_valu).  H mixes the chiralities only through T, whose input has the other
-// chirality, so a matrix applied before the hop can be moved behind it: with premix P and
-// output matrix M, chirality c takes M_c P_c on D and M_c P_(1-c) on T (SPLIT; otherwise one
-// matrix serves both parts and they are summed first).
+// out = M_D D + M_T T (+ post), D and T the two parts of the hop (see wave_hop_valu).  H mixes
+// the chiralities only through T, whose input has the other chirality, so a matrix applied
+// before the hop can be moved behind it: with premix P and output matrix M, chirality c takes
+// M_c P_c on D and M_c P_(1-c) on T (SPLIT; otherwise one matrix serves both parts and they are
+// summed first).
 //
 // What bounds it.  BF16 on a full chip (16^3 x 32, L_s = 16): issue, not memory - 26 and 36 us
 // of bytes at 5.2 TB/s (138 and 188 MB); 28 matrix instructions a site in the first hop (12 of
-// the hop, 16 of the mix) and 20 in the second, and 101 and 135 vector ones for gathers,
-// staging, x term and norm, take 36 and 39 us, against 47 us and a premix pass of 20 us of
+// the hop, 16 of the mix) and 20 in the second, and 99 and 136 vector ones for gathers,
+// staging, x term and norm, take 36 and 38 us, against 47 us and a premix pass of 20 us of
 // hop_mix_kernel.  Not kept: a persistent grid (50 us where this took 46), double-buffered
 // neighbours (46: the registers cost a wave per SIMD), a three-way BF16 split of the mix (44
 // against 44).  Five waves per SIMD; six spill (72 us).
@@ -830,7 +831,7 @@ __global__ void __launch_bounds__(256) vec_update2_kernel(typename S::elem* __re
 // canonical links -> the gathered links of both parities, [parity][cb][8][9]: the hop of
 // direction dir multiplies the neighbour by E = U_mu(x) (dir = mu) or U_mu(x - mu)^dag
 // (dir = 4 + mu), the antiperiodic phase folded in.  FP64 / FP32: rows E[a][b]; BF16: columns
-// first, E[b][a] at [a][b] (the operand order of wave_link_ops).
+// first, E[b][a] at [a][b] (the order in which wave_stage_links lays out the operands).
 template <typename S>
 __global__ void __launch_bounds__(256) gather_links_kernel(typename S::elem* __restrict__ dst,
                                                            const double2* __restrict__ src, int Lx, int Ly, int Lz,
