@@ -541,9 +541,53 @@ def stream_reference_gbs(torch, dev, reps=20):
     return 3 * n * 4 / s / 1e9
 
 
+# dense BF16 peak of the matrix cores
+MFMA_BF16_PEAK_TFLOPS = 2500.0
+
+
+def wave_pair_us(tuned):
+    """Time of the wave hop's pair in an autotuned precision, or None where D_bb of one field
+    runs the site-block hop: the autotuner reports that pair's time for every tile and
+    order of the sweeps (include/dwa.h, dwa_tune_entry)."""
+    us = [c[3] for c in tuned.get("candidates", []) if c[2] == "sweep" and c[3] >= 0]
+    return us[0] if len(us) > 1 and len(set(us)) == 1 else None
+
+
+def make_wave_roofline(pair_us, inner, dims, Ls, S, L, stream_gbs=None):
+    """Roofline record of the wave hop (wave_hop_kernel), which runs the inner solver's D_bb
+    where wave_pair_us gives a time: its pair of launches (N H B G, then x - 1/4 G^-1 I^-1 H),
+    with all fifth-dimension matrices.  Algorithmic bytes 5S + 2L (in, red out and in, x, out;
+    the links twice), flops two hops and dense matrices of L_s (two in the first hop, one in the
+    second), against HBM and the matrix cores' dense BF16 peak, on which BF16 fields are
+    multiplied; instructions, not either of the two, are what it waits for."""
+    V = int(np.prod(dims))
+    nbytes = 5 * S[inner] + 2 * L[inner]
+    flops = V // 2 * Ls * (2 * HOP_FLOPS + 3 * 4 * Ls * 12)
+    gbs, tflops = nbytes / pair_us / 1e3, flops / pair_us / 1e6
+    intensity, balance = flops / nbytes, MFMA_BF16_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS
+    return {"bound": "hbm" if intensity < balance else "mfma",
+            "kernel": f"wave_hop_kernel<{inner.upper()}>, L_s = {Ls}: the two launches of D_bb "
+                      "(Wilson hops with the fifth-dimension matrices)",
+            "pair_us": round(pair_us, 2), "bytes_per_pair": nbytes,
+            "timing": "dwa_autotune: HIP events over repeated pairs on fields in the solver's layout",
+            "traffic": measured_wave_traffic(inner),
+            "arithmetic_intensity_flop_per_byte": round(intensity, 2),
+            "machine_balance_flop_per_byte": round(balance, 2),
+            "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(gbs / HBM_PEAK_GBS, 4),
+            "hbm": {"achieved_gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
+                    "stream_ref_gbs": round(stream_gbs, 1) if stream_gbs else None,
+                    "frac_of_stream_ref": round(gbs / stream_gbs, 4) if stream_gbs else None},
+            "mfma": {"algorithmic_flops_per_pair": flops, "achieved_tflops": round(tflops, 2),
+                     "peak_tflops": MFMA_BF16_PEAK_TFLOPS,
+                     "frac_algorithmic": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4)}}
+
+
 def make_roofline(kern, tuning, inner, dims, Ls, S, L, stream_gbs=None):
-    """Roofline record of the dominant kernel (the first hop of D_bb in the inner
-    precision, hop_mix_kernel MODE 0 with the N mix), against both resources it can be
+    """Roofline record of the kernel that dominates the timed solve: make_wave_roofline's where
+    the inner solver runs the wave hop (then with the record below as "site_block_hop" and
+    its per_precision), and otherwise the first hop of D_bb in the inner
+    precision (hop_mix_kernel MODE 0 with the N mix), against both resources it can be
     bound by: HBM bytes (algorithmic 2S + L per launch, timed as inside a solve and cold)
     and VALU arithmetic (algorithmic flops; beside them the VALU issue fraction from the
     committed SQ_INSTS_VALU count per launch, when it was taken on the kernel source built
@@ -597,24 +641,38 @@ def make_roofline(kern, tuning, inner, dims, Ls, S, L, stream_gbs=None):
     else:
         rec.update(achieved=round(dom["hop_gbs"], 1), peak=HBM_PEAK_GBS, unit="GB/s",
                    frac=round(hbm_frac, 4))
-    return rec
+    pair_us = wave_pair_us(tuning[inner])
+    if pair_us is None:
+        return rec
+    wave = make_wave_roofline(pair_us, inner, dims, Ls, S, L, stream_gbs)
+    wave["per_precision"] = rec.pop("per_precision")
+    wave["site_block_hop"] = rec
+    return wave
+
+
+def _source_sha(name, end=None):
+    """sha256 prefix of a kernel header, or of its text before the line `end`."""
+    import hashlib
+    here = os.path.dirname(os.path.abspath(__file__))
+    text = open(os.path.join(here, "paper_1501_04950_amd", "csrc", name), "rb").read()
+    if end:
+        at = text.index(end)
+        text = text[:at]
+    return hashlib.sha256(text).hexdigest()[:16]
 
 
 def _kernel_sha():
-    import hashlib
-    here = os.path.dirname(os.path.abspath(__file__))
-    h = hashlib.sha256()
-    for f in ("kcommon.h", "khop.h"):
-        h.update(open(os.path.join(here, "paper_1501_04950_amd", "csrc", f), "rb").read())
-    return h.hexdigest()[:16]
+    # what hop_mix_kernel is compiled from: kcommon.h before the site-local kernels and the CG
+    # updates, which follow it
+    return _source_sha("kcommon.h", b"#define DWA_SITE_THREAD")
 
 
-def _profile_value(fname, key, kernel):
+def _profile_value(fname, key, kernel, sha=None):
     """The per-launch figure `key` of `kernel` from a committed counter summary, or None
     when the summary was taken on a different kernel source than the one built here."""
     here = os.path.dirname(os.path.abspath(__file__))
     try:
-        sha = _kernel_sha()
+        sha = sha or _kernel_sha()
         for line in open(os.path.join(here, "profiles", fname)):
             f = line.split()
             if f[:1] == [key] and " ".join(f[1:-3]) == kernel:
@@ -630,6 +688,11 @@ def measured_valu(kernel):
 
 def measured_traffic(kernel):
     return _profile_value("hop_mix_kernel_16x16x16x32_ls16_traffic.md", "traffic_bytes_per_launch", kernel)
+
+
+def measured_wave_traffic(prec):
+    return _profile_value("wave_hop_kernel_16x16x16x32_ls16.md", "traffic_bytes_per_pair",
+                          f"wave_hop_kernel<{prec.upper()}>", _source_sha("kwave.h"))
 
 
 def _cpu_model():
