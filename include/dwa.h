@@ -179,8 +179,8 @@ int dwa_apply_Dbb_static(dwa_ctx *ctx, int prec, void *out_b, const void *in_b);
  * on every slice, and M_kind is a fifth-dimension matrix of dwa_debug_smatrix (kinds
  * 0..6; 0 = identity runs the hop alone).  D_bb is built from two such launches
  * (kinds 2 and 3) and D_bb^dag from kinds 5 and 6, except where a hop with one wavefront
- * per site is the faster one (small lattices, many BF16 calls, and odd Ls up to 15), which
- * applies the same matrices in another order.  Half fields of precision prec;
+ * per site is the faster one (small lattices, many BF16 calls, and up to Ls = 15 most of those
+ * without kernels of their own), which applies the same matrices in another order.  Half fields of precision prec;
  * out and in must not overlap.  Exposed for measurement and tests. */
 int dwa_apply_hop(dwa_ctx *ctx, int prec, int parity_out, int kind, void *out, const void *in);
 

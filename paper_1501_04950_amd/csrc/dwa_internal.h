@@ -395,10 +395,13 @@ inline int hop_sites_per_block(const dwa_ctx* ctx, int prec) {
 //     8 x 12^2 x 16, L_s = 12, 110592 sites 141 -> 152).
 // Solvers keep their fields site-major (no premixed fields, elementwise updates).  Their rule
 // takes the lattice alone, so that a field of a batch runs the kernels of its own solve, bit
-// for bit, and the lines are where an iteration of twelve fields is no slower than the
-// site-block hop's: one field would gain on to about 4000 sites (at 512 sites, L_s = 8, FP64:
-// one field 0.70 of the time, twelve 1.09; FP32 0.71 and 1.08; at 256 0.70 and 0.90).  D_bb of
-// the caller's SoA fields pays for its relayout and is chosen by all sites of the call.
+// for bit.  Where L_s has kernels of its own the lines of FP64 and FP32 are drawn for one field
+// and up to four; there twelve take more than the site-block hop's time, which they take less
+// of at half the sites (iteration, wave / site block, 512 sites, L_s = 8: one field 0.70, four
+// 0.82, twelve 1.09 in FP64, 0.71, 0.79 and 1.08 in FP32, at 256 sites 0.70, 0.73 and 0.90 in
+// FP64; 1024 sites, L_s = 12: 0.75, 1.14 and 1.11 in FP64, 0.74, 0.95 and 0.96 in FP32).  Of the
+// L_s without, FP32's lines are where twelve fields are no slower.  D_bb of the caller's SoA
+// fields pays for its relayout and is chosen by all sites of the call.
 constexpr int kWaveMinLs = 2, kWaveMaxLs = 16;
 inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
   constexpr long long always = LLONG_MAX;
@@ -419,8 +422,8 @@ inline long long wave_max_sites(const dwa_ctx* ctx, int prec, bool soa) {
     return soa ? 4096 : 1024;
   }
   if (soa) return 1024;
-  if (prec == DWA_F64) return Ls >= 14 ? 1024 : 320;
-  return Ls >= 12 ? 1024 : 384;
+  if (Ls >= 10) return 1024;
+  return Ls >= 6 ? 512 : 256;
 }
 inline bool wave_ok(const dwa_ctx* ctx, int prec, bool soa, long long sites) {
   return sites <= wave_max_sites(ctx, prec, soa) && !use_dense(ctx, prec) && ctx->prec[prec].wlinks;

@@ -122,8 +122,9 @@ DBB_LINES = [((8, 8, 8, 8), 2, "f32", 8, True), ((8, 8, 8, 8), 3, "f32", 9, Fals
              ((16, 16, 16, 16), 5, "f64", 1, True), ((16, 16, 16, 16), 2, "bf16", 1, True),
              ((8, 8, 8, 8), 12, "bf16", 42, True), ((8, 8, 8, 8), 12, "bf16", 43, False)]
 SOLVE_LINES = [((6, 6, 6, 12), 3, "f32", True), ((8, 8, 8, 8), 3, "f32", False), ((8, 8, 8, 8), 3, "f64", True),
-               ((4, 4, 4, 10), 8, "f64", True), ((4, 4, 4, 12), 8, "f64", False), ((8, 4, 4, 8), 12, "f64", False),
-               ((8, 4, 8, 8), 14, "f64", True), ((6, 4, 4, 8), 10, "f32", True), ((4, 4, 4, 14), 10, "f32", False),
+               ((8, 4, 4, 8), 8, "f64", True), ((8, 4, 4, 10), 8, "f64", False), ((4, 4, 4, 8), 4, "f64", True),
+               ((4, 4, 4, 10), 4, "f64", False), ((8, 4, 4, 8), 6, "f32", True), ((8, 4, 4, 10), 6, "f32", False),
+               ((8, 4, 8, 8), 10, "f64", True), ((8, 4, 8, 10), 14, "f64", False), ((8, 4, 8, 10), 12, "f32", False),
                ((8, 4, 8, 8), 12, "f32", True), ((8, 8, 8, 8), 5, "f32", True), ((8, 8, 8, 8), 8, "bf16", True),
                ((8, 8, 8, 10), 8, "bf16", False), ((8, 8, 8, 10), 12, "bf16", True)]
 
