@@ -208,7 +208,8 @@ typedef struct {
                 cannot run here (its LDS exceeds the device limit).  Where D_bb of one
                 field runs the hop with one wavefront per site, every entry with dense = 0
                 and nrhs = 1 holds the time of that hop's pair, on fields in its layout;
-                entries of a batch are always the site-block hop's. */
+                entries of a batch are always the site-block hop's, and there are
+                none where no batch runs it. */
 } dwa_tune_entry;
 
 /* Autotuner: time every tile and order of precision prec on this context's lattice,

@@ -1834,9 +1834,12 @@ int dwa_autotune(dwa_ctx* ctx, int prec, int reps, dwa_tune_entry* entries, int 
     for (size_t k = 0; k < cands.size(); ++k)
       if (cands[k].site_us >= 0 && cands[k].site_us < cands[size_t(best)].site_us) best = (long long)k;
   HopTune chosen = best >= 0 ? cands[size_t(best)].t : saved;
-  // fields per block, on a batch of up to 12 fields when one is reserved
+  // fields per block, on a batch of up to 12 fields when one is reserved (no batch runs the
+  // site-block hop where the wave hop serves any number of sites)
   const int nb = std::min(ctx->batch.nmax, 12);
-  if (rc == DWA_OK && best >= 0 && nb >= 2) {
+  ctx->tune[prec] = chosen;
+  const bool no_blocks = use_wave_soa(ctx, prec, 1) && wave_max_sites(ctx, prec, true) == LLONG_MAX;
+  if (rc == DWA_OK && best >= 0 && nb >= 2 && !no_blocks) {
     BatchWs& w = ctx->batch;
     void* x = p64 ? w.f64[B_OPB] : w.lo[prec][BL_W];
     void* t = p64 ? w.f64[B_OPR] : w.lo[prec][BL_T];

@@ -63,19 +63,25 @@ def test_refused_cache_entry_is_tuned_again(tmp_path):
 
 def test_fields_per_block_are_timed_by_the_hop_that_has_them(monkeypatch):
     """The autotuner's times of the fields per block are the site-block hop's, also where this
-    batch runs the wave hop (which takes about 0.4 of its time here)."""
-    dims, Ls = (8, 8, 8, 8), 9
+    batch runs the wave hop (which takes about 0.6 of its time here and leaves larger ones to
+    it); none are taken where the wave hop runs every batch."""
+    dims, Ls = (4, 4, 4, 4), 4
     ctx = context(dims, Ls, 12)
     monkeypatch.setenv("DWA_NO_WAVE_HOP", "1")
     ref = context(dims, Ls, 12)
     us = []
     for c in (ctx, ref):
-        t = c.autotune("bf16", reps=10)["candidates"]
+        t = c.autotune("bf16", reps=30)["candidates"]
         us.append(min(e["us"] for e in t if e["nrhs"] > 1 and e["us"] >= 0))
     print(f"[gpu] fields per block: {us[0]:.1f} us, without the wave hop {us[1]:.1f}", flush=True)
-    assert us[0] > 0.7 * us[1]
+    assert us[0] > 0.8 * us[1]
     ctx.close()
     ref.close()
+    monkeypatch.delenv("DWA_NO_WAVE_HOP")
+    ctx = context(dims, 9, 12)
+    t = ctx.autotune("bf16", reps=2)
+    assert t["nf"] == 1 and {e["nrhs"] for e in t["candidates"]} == {1}
+    ctx.close()
 
 
 def test_wave_solve_does_not_depend_on_the_order():
