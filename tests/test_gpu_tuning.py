@@ -69,10 +69,11 @@ def test_fields_per_block_are_timed_by_the_hop_that_has_them(monkeypatch):
     ctx = context(dims, Ls, 12)
     monkeypatch.setenv("DWA_NO_WAVE_HOP", "1")
     ref = context(dims, Ls, 12)
-    us = []
-    for c in (ctx, ref):
-        t = c.autotune("bf16", reps=30)["candidates"]
-        us.append(min(e["us"] for e in t if e["nrhs"] > 1 and e["us"] >= 0))
+    us = [1e9, 1e9]
+    for _ in range(3):
+        for k, c in enumerate((ctx, ref)):
+            t = c.autotune("bf16", reps=30)["candidates"]
+            us[k] = min([us[k]] + [e["us"] for e in t if e["nrhs"] > 1 and e["us"] >= 0])
     print(f"[gpu] fields per block: {us[0]:.1f} us, without the wave hop {us[1]:.1f}", flush=True)
     assert us[0] > 0.8 * us[1]
     ctx.close()
